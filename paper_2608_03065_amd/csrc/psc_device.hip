@@ -548,16 +548,7 @@ walk_gather_kernel(const int32_t *__restrict__ table, const uint32_t *__restrict
 constexpr uint16_t kBf16NegInf = 0xFF80u;
 constexpr uint32_t kF32NegInf = 0xFF800000u;
 
-// One wavefront applies kWordsPerWave consecutive mask words to the logits
-// they cover (the row length V is a multiple of 32 and the logits are 16-byte
-// aligned, so word w covers exactly the 32 elements at 32*w).  Lane j holds
-// word j in `m` (all ones past the end: nothing to do).  The wavefront writes
-// its 64 (bf16) or 32 (fp32) words as kVecs contiguous 1 KiB vector stores;
-// lanes get their 8 (bf16) or 4 (fp32) mask bits from the owning lane by a
-// cross-lane shuffle.  Entries whose bit is set are never touched: an
-// all-zero group is one store of -inf, a mixed group is a read-select-write
-// of that 16-byte vector only (all of a lane's reads are issued before its
-// stores).
+// One 16-byte vector group of the speculative step: kVecs vectors per lane.
 template <bool kBf16>
 struct ApplyGeom {
     static constexpr int kPerVec = kBf16 ? 8 : 4;           // elements per 16-byte vector
@@ -566,82 +557,222 @@ struct ApplyGeom {
     static constexpr int kWordsPerWave = kWave * kVecs / kVecsPerWord;
 };
 
+constexpr uint32_t kNegInf2 = 0xFF80FF80u;   // two bf16
+constexpr int kTileBytes = 4096;
+constexpr int kLineBytes = 128;
+// Cache policies of the logits stores: written through the XCD's L2 at device
+// scope (sc1), nontemporal for lines written whole (they need not stay in the
+// Infinity Cache) and temporal for partial ones (they should).
+constexpr int kPolicyStream = kPolicyNt | 16, kPolicyMerge = 16;
+
+template <bool kBf16, int kPolicy>
+__device__ __forceinline__ void store_inf(__amdgpu_buffer_rsrc_t rsrc, uint32_t at) {
+    if (kBf16) __builtin_amdgcn_raw_buffer_store_b16((short)kBf16NegInf, rsrc, at, 0, kPolicy);
+    else __builtin_amdgcn_raw_buffer_store_b32(kF32NegInf, rsrc, at, 0, kPolicy);
+}
+
+// ---------------------------------------------------------------- masking a tile
 //
-// The loads and stores go through a buffer resource over the wavefront's
-// `bytes` bytes of logits.  A lane that must not touch its vector gets an
-// offset past the end instead of a branch: the hardware drops such an access
-// (a load returns zeros) without a memory request.  Every memory instruction
-// is then issued unconditionally, so the compiler counts them exactly: the
-// selects wait for their loads only, and no store waits for an earlier
-// store to complete (with branches it had to wait for all outstanding
-// accesses before each vector, which serialised the stores).
+// One wavefront masks one tile of a logits row: kTileBytes of memory, cut at
+// 128-byte lines (not at the row's start, which is at any element address
+// when V is odd).  Masking needs no old value, so a tile is masked with
+// stores alone: the mask bits are the same for the whole wavefront, lane l
+// stands for element l of a 64-element step, and the complement of the
+// step's 64 mask bits is the store's execution mask.  No load of logits, no
+// wait, and any row alignment costs two mask words per lane instead of one.
+//
+// What a store costs depends on where the line is (64 sequences x 151,936
+// bf16 logits, single launch, us; resident: the buffers in turn fit the 256 MB
+// Infinity Cache, as logits do that the step before has just written; cold:
+// they do not):
+//                                   resident      cold        (step)
+//   read, select, write vectors         7.5        7.6     schema JSON
+//   all stores nontemporal              6.8        6.9
+//   all stores cached                   5.4        9.0
+//   full lines nontemporal,             5.6        5.9     <- done here
+//     partial ones cached
+// A fully masked line is written through to HBM at once; a partial one is
+// left to the Infinity Cache, where merging it costs nothing while it stays
+// there.  Only a batch whose partial lines do not fit it pays for them again,
+// as reads and writes of HBM: then (`select_dense`) a tile in which most words
+// are densely mixed is read, selected and written in 16-byte vectors instead
+// (256 x 262,144 bf16 of a programming language: 44 us against 62; of
+// generic JSON, sparsely masked: 39 against 32, and the stores stay).
 template <bool kBf16>
-__device__ __forceinline__ void apply_words(uint4 *__restrict__ base, uint32_t bytes, uint32_t m, int lane) {
-    using G = ApplyGeom<kBf16>;
-    constexpr uint32_t kFull = (1u << G::kPerVec) - 1;
-    const __amdgpu_buffer_rsrc_t rsrc = wave_rsrc(base, bytes);
-    uint32_t g[G::kVecs];
-    u32x4 x[G::kVecs];
-#pragma unroll
-    for (int j = 0; j < G::kVecs; j++) {
-        // vector v = j*64 + lane covers elements [kPerVec*v, kPerVec*v + kPerVec)
-        const int v = j * kWave + lane;
-        g[j] = (__shfl(m, v / G::kVecsPerWord, kWave) >> ((v % G::kVecsPerWord) * G::kPerVec)) & kFull;
+struct Tile {
+    static constexpr int kElem = kBf16 ? 2 : 4;             // bytes per element
+    static constexpr int kPerVec = 16 / kElem;              // elements per 16-byte vector
+    static constexpr int kElems = kTileBytes / kElem;
+    static constexpr int kWords = kElems / 32;              // mask words, at most one per lane
+    static constexpr int kVecsPerWord = 32 / kPerVec;
+};
+
+// Row b of the logits: `line` is the 128-byte line that holds its first
+// element, the delta elements before it there belong to the row above.
+template <bool kBf16>
+struct Row {
+    char *line;
+    int32_t delta, V;
+    int32_t before;    // mask words the tiles' words are shifted by: ceil(delta / 32)
+    int32_t shift;     // bit of its first mask word that a lane's 32 elements start at
+
+    __device__ __forceinline__ Row(void *logits, int64_t b, int32_t n) : V(n) {
+        const uintptr_t addr = reinterpret_cast<uintptr_t>(logits) + (uintptr_t)b * (uintptr_t)n * Tile<kBf16>::kElem;
+        line = reinterpret_cast<char *>(addr & ~(uintptr_t)(kLineBytes - 1));
+        delta = (int32_t)(addr & (kLineBytes - 1)) / Tile<kBf16>::kElem;
+        before = (delta + 31) / 32;
+        shift = before * 32 - delta;
     }
+};
+
+// Tiles that hold any row of V elements; `lines`: every row starts at a line.
+template <bool kBf16>
+constexpr int32_t row_tiles(int32_t V, bool lines) {
+    const int32_t before = lines ? 0 : (kLineBytes / Tile<kBf16>::kElem - 1 + 31) / 32;
+    return (int32_t)(((int64_t)V + 31) / 32 + before + Tile<kBf16>::kWords - 1) / Tile<kBf16>::kWords;
+}
+
+// The -inf select of one 16-byte vector: element k is kept where bit k of g is 1.
+template <bool kBf16>
+__device__ __forceinline__ u32x4 mask_vector(u32x4 x, uint32_t g) {
 #pragma unroll
-    for (int j = 0; j < G::kVecs; j++) {
-        const uint32_t off = (uint32_t)(j * kWave + lane) * 16u;
-        x[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, g[j] != 0 && g[j] != kFull ? off : kOffSkip, 0,
-                                                     kPolicyNt);
-    }
-#pragma unroll
-    for (int j = 0; j < G::kVecs; j++) {
-        u32x4 val = x[j];
+    for (int k = 0; k < 4; k++) {
         if (kBf16) {
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const uint32_t lo = (g[j] >> (2 * k)) & 1 ? (val[k] & 0xFFFFu) : kBf16NegInf;
-                const uint32_t hi = (g[j] >> (2 * k + 1)) & 1 ? (val[k] >> 16) : kBf16NegInf;
-                val[k] = lo | (hi << 16);
-            }
+            const uint32_t lo = (uint32_t)((int32_t)(g << (31 - 2 * k)) >> 31);
+            const uint32_t hi = (uint32_t)((int32_t)(g << (30 - 2 * k)) >> 31);
+            const uint32_t keep = (lo & 0xFFFFu) | (hi & 0xFFFF0000u);
+            x[k] = (x[k] & keep) | (kNegInf2 & ~keep);
         } else {
-#pragma unroll
-            for (int k = 0; k < 4; k++)
-                if (!((g[j] >> k) & 1)) val[k] = kF32NegInf;
+            x[k] = (g >> k) & 1 ? x[k] : kF32NegInf;
         }
-        const uint32_t off = (uint32_t)(j * kWave + lane) * 16u;
-        __builtin_amdgcn_raw_buffer_store_b128(val, rsrc, g[j] != kFull ? off : kOffSkip, 0, kPolicyStore);
     }
+    return x;
 }
 
-// Fast path of psc_apply_mask: the B rows are one flat run of n_words mask
-// words (V % 32 == 0), split over wavefronts.
+// Whether any of the 4 lanes of this lane's aligned quad has `p`.
+__device__ __forceinline__ bool any_of_quad(bool p) {
+    int x = p;
+    x |= __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
+    x |= __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
+    return x != 0;
+}
+
+// The read-select-write of a whole tile inside the row: lane j of column c
+// holds vector 64 c + j.  A lane that has nothing to do gets an offset past
+// the end instead of a branch: the hardware drops such an access without a
+// memory request.  A 64-byte quad of vectors is written whole or not at all
+// (its kept vectors are read too): with the kept vectors left out, partial
+// lines reached HBM, 50.0 us instead of 44.1 at 256 x 262,144.
+template <bool kBf16>
+__device__ __forceinline__ void select_tile(__amdgpu_buffer_rsrc_t rsrc, uint32_t m, int lane) {
+    using T = Tile<kBf16>;
+    constexpr uint32_t kFull = (1u << T::kPerVec) - 1;
+    constexpr int kVecs = kTileBytes / 16 / kWave;
+    uint32_t g[kVecs], off[kVecs];
+    u32x4 x[kVecs];
+#pragma unroll
+    for (int j = 0; j < kVecs; j++) {
+        const int v = j * kWave + lane;
+        g[j] = (__shfl(m, v / T::kVecsPerWord, kWave) >> ((v % T::kVecsPerWord) * T::kPerVec)) & kFull;
+        off[j] = any_of_quad(g[j] != kFull) ? (uint32_t)v * 16u : kOffSkip;
+        x[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, g[j] != 0 ? off[j] : kOffSkip, 0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < kVecs; j++)
+        __builtin_amdgcn_raw_buffer_store_b128(mask_vector<kBf16>(x[j], g[j]), rsrc, off[j], 0, kPolicyStream);
+}
+
+// Mask tile t of row R: word(w) is the row's mask word w (0 <= w < W); the
+// words also go to out[0 .. W) when it is set.
+template <bool kBf16, class Word>
+__device__ __forceinline__ void mask_tile(const Row<kBf16> &R, int32_t W, int32_t t, bool select_dense, int lane,
+                                          const Word &word, uint32_t *__restrict__ out) {
+    using T = Tile<kBf16>;
+    // lane j < kWords: the bits of elements p0 .. p0 + 31 counted from the line
+    const int64_t w = (int64_t)t * T::kWords + lane - R.before;
+    const bool mine = lane < T::kWords && w >= 0 && w < W;
+    uint32_t lo = 0, hi = 0;
+    if (mine) lo = word((int32_t)w);
+    if (R.shift && lane < T::kWords && w >= -1 && w + 1 < W) hi = word((int32_t)w + 1);
+    uint32_t drop = ~__builtin_amdgcn_alignbit(hi, lo, R.shift);
+    // outside the row nothing is masked
+    const int64_t p0 = ((int64_t)t * T::kWords + lane) * 32, left = (int64_t)R.delta + R.V - p0;
+    if (p0 < R.delta) drop &= R.delta - p0 >= 32 ? 0u : ~0u << (R.delta - p0);
+    if (left < 32) drop &= left <= 0 ? 0u : ~(~0u << left);
+    if (lane >= T::kWords) drop = 0;
+    const __amdgpu_buffer_rsrc_t rsrc = wave_rsrc(R.line + (int64_t)t * kTileBytes, kTileBytes);
+    constexpr uint32_t kInf = kBf16 ? kNegInf2 : kF32NegInf;
+    bool select = false;
+    if (select_dense && (t > 0 || R.delta == 0) && (int64_t)(t + 1) * T::kElems <= (int64_t)R.delta + R.V) {
+        const int bits = __popc(drop);
+        select = __popcll(__ballot(bits >= 8 && bits < 32)) * 2 > __popcll(__ballot(bits > 0 && bits < 32));
+    }
+    if (select) {
+        select_tile<kBf16>(rsrc, ~drop, lane);
+    } else {
+        // the lines masked whole, as 16-byte vectors
+        // (a bf16 line is two words: quad_perm [1,0,3,2] reads the other one)
+        const int other = kBf16 ? __builtin_amdgcn_update_dpp(0, (int)drop, 0xB1, 0xF, 0xF, false) : -1;
+        const bool full = drop == ~0u && other == -1;
+        const uint64_t lines = __ballot(full);
+        const u32x4 inf = {kInf, kInf, kInf, kInf};
+#pragma unroll
+        for (int j = 0; j < kTileBytes / 16 / kWave; j++) {
+            const int v = j * kWave + lane;
+            if ((lines >> (v / T::kVecsPerWord)) & 1)
+                __builtin_amdgcn_raw_buffer_store_b128(inf, rsrc, (uint32_t)v * 16u, 0, kPolicyStream);
+        }
+        // the others, 64 elements a store; straight-line, since a wavefront
+        // pays the latency of every branch itself (rolled into a loop 7.0 us
+        // at 64 x 151,936, a branch per line 6.7, this 6.1)
+        const int rest = full ? 0 : (int)drop;
+        const uint64_t some = __ballot(rest != 0);
+        constexpr int kGroup = 16;   // words
+#pragma unroll
+        for (int i0 = 0; i0 < T::kWords; i0 += kGroup) {
+            if (!((some >> i0) & ((1ull << kGroup) - 1))) continue;
+#pragma unroll
+            for (int i = i0; i < i0 + kGroup; i += 2) {
+                const uint64_t bits = (uint32_t)__builtin_amdgcn_readlane(rest, i) |
+                                      (uint64_t)(uint32_t)__builtin_amdgcn_readlane(rest, i + 1) << 32;
+                if (__builtin_amdgcn_inverse_ballot_w64(bits))
+                    store_inf<kBf16, kPolicyMerge>(rsrc, (uint32_t)(i * 32 + lane) * T::kElem);
+            }
+        }
+    }
+    // last, so that no access of the logits waits for this store
+    if (out && mine) out[w] = lo;
+}
+
+// psc_apply_mask: the tiles of the B rows, split over wavefronts.
 template <bool kBf16>
 __global__ void __launch_bounds__(kBlock)
-apply_fast_kernel(uint4 *__restrict__ logits, const uint32_t *__restrict__ bits, int64_t n_words) {
-    using G = ApplyGeom<kBf16>;
+apply_fast_kernel(void *__restrict__ logits, const uint32_t *__restrict__ bits, int32_t V, int32_t W, uint32_t tiles,
+                  uint64_t n_waves, int32_t select_dense) {
     const int lane = threadIdx.x & (kWave - 1);
-    // the wavefront index is uniform: saying so keeps the buffer resource in
-    // scalar registers
-    const int64_t wave = (int64_t)blockIdx.x * (kBlock / kWave) +
-                         __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t w_base = wave * G::kWordsPerWave;
-    if (w_base >= n_words) return;
-    uint32_t m = 0xFFFFFFFFu;
-    if (lane < G::kWordsPerWave && w_base + lane < n_words) m = bits[w_base + lane];
-    const uint32_t words = (uint32_t)min<int64_t>(G::kWordsPerWave, n_words - w_base);
-    apply_words<kBf16>(logits + w_base * G::kVecsPerWord, words * G::kVecsPerWord * 16u, m, lane);
+    // the wavefront index is uniform: saying so keeps the row in scalar registers
+    const uint64_t wave = (uint64_t)blockIdx.x * (kBlock / kWave) +
+                          (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (wave >= n_waves) return;
+    const uint32_t b = n_waves >> 32 ? (uint32_t)(wave / tiles) : (uint32_t)wave / tiles;
+    const Row<kBf16> R(logits, b, V);
+    const uint32_t *row = bits + (int64_t)b * W;
+    mask_tile<kBf16>(R, W, (int32_t)(wave - (uint64_t)b * tiles), select_dense != 0, lane,
+                     [&](int32_t w) { return row[w]; }, nullptr);
 }
 
-// General path: any V and alignment, one element per thread.
-template <bool kBf16>
+// Short rows, and logits that are not at their elements' own alignment: one
+// element per thread.  A wavefront per tile would be mostly idle on short
+// rows (65,535 rows of 33: 4.8 us here, 15 us there; of 513: 53 against 9.6).
+constexpr int32_t kShortRow = 512;
+
+template <bool kBf16, class Index>
 __global__ void __launch_bounds__(kBlock)
-apply_generic_kernel(void *__restrict__ logits, const uint32_t *__restrict__ bits, int64_t n, int32_t V,
-                     int32_t W) {
-    for (int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x; e < n; e += (int64_t)gridDim.x * kBlock) {
-        const int64_t b = e / V;
-        const int32_t v = (int32_t)(e - b * V);
-        if ((bits[b * W + (v >> 5)] >> (v & 31)) & 1u) continue;
+apply_generic_kernel(void *__restrict__ logits, const uint32_t *__restrict__ bits, Index n, int32_t V, int32_t W) {
+    for (Index e = (Index)blockIdx.x * kBlock + threadIdx.x; e < n; e += (Index)gridDim.x * kBlock) {
+        const Index b = e / (Index)V;
+        const int32_t v = (int32_t)(e - b * (Index)V);
+        if ((bits[(int64_t)b * W + (v >> 5)] >> (v & 31)) & 1u) continue;
         if (kBf16) reinterpret_cast<uint16_t *>(logits)[e] = kBf16NegInf;
         else reinterpret_cast<uint32_t *>(logits)[e] = kF32NegInf;
     }
@@ -649,38 +780,23 @@ apply_generic_kernel(void *__restrict__ logits, const uint32_t *__restrict__ bit
 
 // ---------------------------------------------------------------- fused step
 
-// psc_compute_and_apply, fast path (V % 32 == 0, 16-byte aligned logits):
-// one workgroup per (sequence b, slice of kFusedBlock / kWave *
-// kWordsPerWave mask words).  After the walk, every wavefront loads its words
-// of the class's mask row once, writes them to out_bitmask[b] (when
-// requested) and applies them to logits[b] in place.  One launch instead of
-// two, and the bitmask is not read back from HBM between the gather and the
-// apply.  Four wavefronts per workgroup (2 measured slightly faster on a
-// 200-step schema sample but slower over the 1,000-step schema workload and
-// on the largest one); the walk is repeated per workgroup, which costs
-// latency but no bandwidth.
+// psc_compute_and_apply: one workgroup per (sequence b, kFusedBlock / kWave
+// tiles of its row).  After the walk, every wavefront loads its words of the
+// class's mask row once, writes them to out_bitmask[b] (when requested) and
+// masks its tile of logits[b] in place.
 constexpr int kFusedBlock = 4 * kWave;
 
-// The part of the fused step after the walk: this workgroup's slice of the
+// The part of the fused step after the walk: this workgroup's tiles of the
 // class's mask row, written to out_bitmask[b] and applied to logits[b].
 template <bool kBf16, bool kSliced>
-__device__ __forceinline__ void fused_fast_apply(int cls, int b, const uint32_t *__restrict__ masks,
-                                                 int32_t mask_stride, const int32_t *__restrict__ ids, int32_t W,
-                                                 uint32_t *__restrict__ out, uint4 *__restrict__ logits) {
-    using G = ApplyGeom<kBf16>;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w_base =
-        (blockIdx.x * (kFusedBlock / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave)) * G::kWordsPerWave;
-    if (w_base >= W) return;
-    uint32_t m = 0xFFFFFFFFu;
-    const int w = w_base + lane;
-    const bool mine = lane < G::kWordsPerWave && w < W;
-    if (mine) m = cls < 0 ? 0u : *mask_at<kSliced>(masks, mask_stride, ids, cls, w);
-    const uint32_t words = (uint32_t)min(G::kWordsPerWave, W - w_base);
-    apply_words<kBf16>(logits + ((size_t)b * W + w_base) * G::kVecsPerWord, words * G::kVecsPerWord * 16u, m,
-                       lane);
-    // last, so that the logits accesses never wait for this store
-    if (out && mine) out[(size_t)b * W + w] = m;
+__device__ __forceinline__ void fused_fast_apply(int cls, int b, const Row<kBf16> &R,
+                                                 const uint32_t *__restrict__ masks, int32_t mask_stride,
+                                                 const int32_t *__restrict__ ids, int32_t W, int32_t select_dense,
+                                                 uint32_t *__restrict__ out) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    mask_tile<kBf16>(R, W, blockIdx.x * (kFusedBlock / kWave) + wave, select_dense != 0, threadIdx.x & (kWave - 1),
+                     [&](int32_t w) { return cls < 0 ? 0u : *mask_at<kSliced>(masks, mask_stride, ids, cls, w); },
+                     out ? out + (size_t)b * W : nullptr);
 }
 
 // A timeline record per wavefront (psc_compute_and_apply_timeline): its
@@ -708,14 +824,15 @@ __global__ void __launch_bounds__(kFusedBlock)
 fused_fast_kernel(const int32_t *__restrict__ table, const uint32_t *__restrict__ masks, int32_t mask_stride,
                   const int32_t *__restrict__ ids, int32_t n_lex, int32_t n_lr, const int32_t *__restrict__ stacks,
                   int32_t stride, int64_t n_stack, const int32_t *__restrict__ lens, const int32_t *__restrict__ qs,
-                  int32_t W, uint32_t *__restrict__ out, uint32_t *__restrict__ err, uint4 *__restrict__ logits,
-                  unsigned long long *__restrict__ tl) {
+                  int32_t V, int32_t W, int32_t select_dense, uint32_t *__restrict__ out, uint32_t *__restrict__ err,
+                  void *__restrict__ logits, unsigned long long *__restrict__ tl) {
     unsigned long long t0 = 0, t_b = 0;
     if (kTl) t0 = wall_clock64();
     const int b = blockIdx.y;
+    const Row<kBf16> R(logits, b, V);
     const int cls = block_class(table, n_lex, n_lr, stacks, stride, n_stack, lens, qs, b, err);
     if (kTl) t_b = wall_clock64();
-    fused_fast_apply<kBf16, kSliced>(cls, b, masks, mask_stride, ids, W, out, logits);
+    fused_fast_apply<kBf16, kSliced>(cls, b, R, masks, mask_stride, ids, W, select_dense, out);
     if (kTl && (threadIdx.x & (kWave - 1)) == 0) timeline_record(tl, t0, t0, t_b, 0u, 0u);
 }
 
@@ -1295,11 +1412,12 @@ advance_copy_kernel(DecodeArgs D) {
 template <bool kBf16, bool kSliced>
 __global__ void __launch_bounds__(kFusedBlock)
 decode_fast_kernel(const int32_t *__restrict__ table, const uint32_t *__restrict__ masks, int32_t mask_stride,
-                   const int32_t *__restrict__ ids, DecodeArgs D, int32_t W, uint32_t *__restrict__ out,
-                   uint32_t *__restrict__ err, uint4 *__restrict__ logits) {
+                   const int32_t *__restrict__ ids, DecodeArgs D, int32_t V, int32_t W, int32_t select_dense,
+                   uint32_t *__restrict__ out, uint32_t *__restrict__ err, void *__restrict__ logits) {
     const int b = blockIdx.y;
+    const Row<kBf16> R(logits, b, V);
     const int cls = decode_block_class(table, D, b, err);
-    fused_fast_apply<kBf16, kSliced>(cls, b, masks, mask_stride, ids, W, out, logits);
+    fused_fast_apply<kBf16, kSliced>(cls, b, R, masks, mask_stride, ids, W, select_dense, out);
 }
 
 template <bool kBf16, bool kSliced>
@@ -1431,6 +1549,31 @@ psc_status launch_classes(const psc_handle *h, const int32_t *stacks, int32_t st
     return launched(what);
 }
 
+// Whether the vector path takes rows of V logits: their elements at their own
+// alignment (any address a bf16 or fp32 tensor can have).
+bool vector_path(const void *logits, bool bf16) {
+    return (reinterpret_cast<uintptr_t>(logits) & (bf16 ? 1 : 3)) == 0;
+}
+// Whether every row starts at a 128-byte line.
+bool line_rows(const void *logits, bool bf16, int32_t V) {
+    return (reinterpret_cast<uintptr_t>(logits) & (kLineBytes - 1)) == 0 && V % (kLineBytes / (bf16 ? 2 : 4)) == 0;
+}
+int32_t tiles_of(const void *logits, bool bf16, int32_t V) {
+    const bool lines = line_rows(logits, bf16, V);
+    return bf16 ? row_tiles<true>(V, lines) : row_tiles<false>(V, lines);
+}
+// The same wherever the rows start: the timeline's records are counted
+// before the logits are known.
+int32_t most_tiles(bool bf16, int32_t V) { return bf16 ? row_tiles<true>(V, false) : row_tiles<false>(V, false); }
+// Whether a call's densely mixed tiles are read, selected and written
+// (mask_tile): batches above kLargeBytes of logits, whose partial lines do not
+// stay in the Infinity Cache.  Three buffers used in turn, dense masks of a
+// programming language, stores alone against this: 109 MB 34.5 and 36.6 us
+// (bf16), 101 MB 25.1 and 33.0 (fp32); 117 MB 50.1 and 39.7; 134 MB 61.9 and
+// 44.3.
+constexpr int64_t kLargeBytes = (int64_t)104 << 20;
+bool large_batch(bool bf16, int32_t B, int32_t V) { return (int64_t)B * V * (bf16 ? 2 : 4) > kLargeBytes; }
+
 // Words of the mask row per fused workgroup on the fast path.
 int32_t fused_words_per_block(bool bf16) {
     return (kFusedBlock / kWave) * (bf16 ? ApplyGeom<true>::kWordsPerWave : ApplyGeom<false>::kWordsPerWave);
@@ -1447,7 +1590,8 @@ struct FastArgs {
     const int32_t *lens, *qs;
     int32_t W;
     uint32_t *out;
-    uint4 *logits;
+    void *logits;
+    int32_t V, select_dense;
     unsigned long long *tl;
 };
 
@@ -1457,11 +1601,11 @@ void launch_fast(bool spec, const FastArgs &F) {
     if (spec)
         hipLaunchKernelGGL((fused_spec_kernel<kBf16, kSliced, kTl>), F.grid, dim3(kFusedBlock), 0, F.s, T.table,
                            T.masks, T.mstride, T.ids, F.n_lex, F.n_lr, F.n_classes, F.stacks, F.stride, F.n_stack,
-                           F.lens, F.qs, F.W, F.out, T.err, T.pred, F.logits, F.tl);
+                           F.lens, F.qs, F.W, F.out, T.err, T.pred, reinterpret_cast<uint4 *>(F.logits), F.tl);
     else
         hipLaunchKernelGGL((fused_fast_kernel<kBf16, kSliced, kTl>), F.grid, dim3(kFusedBlock), 0, F.s, T.table,
                            T.masks, T.mstride, T.ids, F.n_lex, F.n_lr, F.stacks, F.stride, F.n_stack, F.lens, F.qs,
-                           F.W, F.out, T.err, F.logits, F.tl);
+                           F.V, F.W, F.select_dense, F.out, T.err, F.logits, F.tl);
 }
 
 template <bool kBf16>
@@ -1476,11 +1620,11 @@ void launch_fast_dtype(bool spec, bool sliced, bool tl, const FastArgs &F) {
 }
 
 // The single-launch step for ragged (stride 0) or strided stacks; with
-// `tl` (fast path only) the timeline variant.
+// `tl` (V % 32 == 0 and 16-byte aligned logits only) the timeline variant.
 psc_status launch_fused(const psc_handle *h, const int32_t *stacks, int32_t stride, int64_t n_stack,
                         const int32_t *stack_lens, const int32_t *lexer_states, int32_t B, uint32_t *out_bitmask,
                         void *logits, psc_dtype dtype, int32_t V, void *stream, const char *what,
-                        unsigned long long *tl = nullptr, int64_t n_tl = 0) {
+                        unsigned long long *tl = nullptr, int64_t n_tl = 0, bool buffer_per_step = false) {
     // out_bitmask may be null: the logits stand in for it in the null check
     if (psc_status st = check_states(h, stacks, stride, n_stack, stack_lens, lexer_states, B,
                                      out_bitmask ? static_cast<const void *>(out_bitmask) : logits, what))
@@ -1490,8 +1634,7 @@ psc_status launch_fused(const psc_handle *h, const int32_t *stacks, int32_t stri
     const bool fast = (V % 32 == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15) == 0);
     const int32_t W = h->W;
     if (tl) {
-        const int64_t need = (int64_t)((W + fused_words_per_block(bf16) - 1) / fused_words_per_block(bf16)) * B *
-                             (kFusedBlock / kWave);
+        const int64_t need = psc_timeline_records(h, B, dtype);
         if (!fast || n_tl < need) {
             set_error(std::string(what) + ": the timeline needs the fast path (V % 32 == 0, 16-byte aligned "
                       "logits) and " + std::to_string(need) + " records");
@@ -1501,11 +1644,14 @@ psc_status launch_fused(const psc_handle *h, const int32_t *stacks, int32_t stri
     if (B == 0) return PSC_OK;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const Bound T = bound(h);
-    if (fast) {
-        const FastArgs F{dim3((W + fused_words_per_block(bf16) - 1) / fused_words_per_block(bf16), B), s, T,
-                         h->n_lex, h->n_lr, h->n_classes, stacks, stride, n_stack, stack_lens, lexer_states, W,
-                         out_bitmask, reinterpret_cast<uint4 *>(logits), tl};
-        const bool spec = (h->options & PSC_OPT_SPECULATE) != 0;
+    if (vector_path(logits, bf16)) {
+        const bool spec = fast && (h->options & PSC_OPT_SPECULATE) != 0;
+        const int32_t per = kFusedBlock / kWave;
+        const int32_t tiles = tl ? most_tiles(bf16, V) : tiles_of(logits, bf16, V);
+        const unsigned segments = spec && !tl ? (W + fused_words_per_block(bf16) - 1) / fused_words_per_block(bf16)
+                                              : (tiles + per - 1) / per;
+        const FastArgs F{dim3(segments, B), s, T, h->n_lex, h->n_lr, h->n_classes, stacks, stride, n_stack, stack_lens,
+                         lexer_states, W, out_bitmask, logits, V, buffer_per_step || large_batch(bf16, B, V), tl};
         if (bf16) launch_fast_dtype<true>(spec, T.sliced, tl != nullptr, F);
         else launch_fast_dtype<false>(spec, T.sliced, tl != nullptr, F);
     } else {
@@ -1751,8 +1897,8 @@ extern "C" psc_status psc_compute_and_apply_n(const psc_handle *h, const int32_t
 
 extern "C" int64_t psc_timeline_records(const psc_handle *h, int32_t B, psc_dtype dtype) {
     if (!h || B < 0) return 0;
-    const int32_t per = fused_words_per_block(dtype == PSC_BF16);
-    return (int64_t)((h->W + per - 1) / per) * B * (kFusedBlock / kWave);
+    const int32_t per = kFusedBlock / kWave;
+    return (int64_t)((most_tiles(dtype == PSC_BF16, h->V) + per - 1) / per) * B * per;
 }
 
 extern "C" psc_status psc_compute_and_apply_timeline(const psc_handle *h, const int32_t *stacks, int64_t n_stack,
@@ -1934,36 +2080,31 @@ extern "C" psc_status psc_decode_step(const psc_handle *h, const int32_t *stacks
     const DecodeArgs D{adv_tables(h), stacks_in, lens_in, qs_in, stacks_out, lens_out, qs_out, tokens, status, cap};
     const int32_t W = h->W;
     const bool bf16 = dtype == PSC_BF16;
-    const bool fast = (V % 32 == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15) == 0);
+    const bool fast = vector_path(logits, bf16);
     // When the fused grid does not fit on the GPU at once, workgroups that
     // start late would repeat the advance after the early ones finished:
     // then the advance runs once per sequence in a launch of its own and the
     // fused step follows on the new states (same results).
-    const int words_per_block = !fast ? kGenWords
-                                      : (kFusedBlock / kWave) * (bf16 ? ApplyGeom<true>::kWordsPerWave
-                                                                      : ApplyGeom<false>::kWordsPerWave);
-    const int64_t n_blocks = (int64_t)((W + words_per_block - 1) / words_per_block) * B;
-    if (n_blocks > resident_blocks()) {
+    const int waves = kFusedBlock / kWave;
+    const int64_t segments = fast ? (tiles_of(logits, bf16, V) + waves - 1) / waves : (W + kGenWords - 1) / kGenWords;
+    if (segments * B > resident_blocks()) {
         hipLaunchKernelGGL(advance_copy_kernel, dim3(B), dim3(kWave), 0, s, D);
         hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return device_fail(what, e0);
         return launch_fused(h, stacks_out, cap, kUnbounded, lens_out, qs_out, B, out_bitmask, logits, dtype, V, stream,
-                            what);
+                            what, nullptr, 0, true);
     }
+    const dim3 grid((unsigned)segments, B);
     if (fast) {
-        const int words_per_block = (kFusedBlock / kWave) * (bf16 ? ApplyGeom<true>::kWordsPerWave
-                                                                  : ApplyGeom<false>::kWordsPerWave);
-        dim3 grid((W + words_per_block - 1) / words_per_block, B);
 #define PSC_DECODE_FAST(BF, SL)                                                                                      \
     hipLaunchKernelGGL((decode_fast_kernel<BF, SL>), grid, dim3(kFusedBlock), 0, s, T.table, T.masks, T.mstride, T.ids, \
-                       D, W, out_bitmask, T.err, reinterpret_cast<uint4 *>(logits))
+                       D, V, W, 1, out_bitmask, T.err, logits)
         if (bf16 && T.sliced) PSC_DECODE_FAST(true, true);
         else if (bf16) PSC_DECODE_FAST(true, false);
         else if (T.sliced) PSC_DECODE_FAST(false, true);
         else PSC_DECODE_FAST(false, false);
 #undef PSC_DECODE_FAST
     } else {
-        dim3 grid((W + kGenWords - 1) / kGenWords, B);
 #define PSC_DECODE_GEN(BF, SL)                                                                                       \
     hipLaunchKernelGGL((decode_generic_kernel<BF, SL>), grid, dim3(kBlock), 0, s, T.table, T.masks, T.mstride, T.ids,   \
                        D, V, W, out_bitmask, T.err, logits)
@@ -1990,32 +2131,40 @@ extern "C" psc_status psc_apply_mask(void *logits, psc_dtype dtype, const uint32
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const bool bf16 = dtype == PSC_BF16;
+    // rows of whole words are one long row: the bits are contiguous as well
+    if (V % 32 == 0 && (int64_t)B * V <= INT32_MAX) {
+        V *= B;
+        B = 1;
+    }
     const int32_t W = (V + 31) / 32;
-    const bool fast = (V % 32 == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15) == 0);
-    if (fast) {
-        const int64_t n_words = (int64_t)B * W;
-        const int64_t words_per_wave = bf16 ? ApplyGeom<true>::kWordsPerWave : ApplyGeom<false>::kWordsPerWave;
-        const int64_t waves = (n_words + words_per_wave - 1) / words_per_wave;
-        const int64_t blocks = (waves + (kBlock / kWave) - 1) / (kBlock / kWave);
+    if (V >= kShortRow && vector_path(logits, bf16)) {
+        const uint32_t tiles = (uint32_t)tiles_of(logits, bf16, V);
+        const uint64_t waves = (uint64_t)tiles * B;
+        const uint64_t blocks = (waves + kBlock / kWave - 1) / (kBlock / kWave);
         if (blocks > 0x7FFFFFFF) {
             set_error("psc_apply_mask: tensor too large");
             return PSC_E_INVALID_ARG;
         }
+        const int32_t select_dense = large_batch(bf16, B, V);
         if (bf16)
-            hipLaunchKernelGGL(apply_fast_kernel<true>, dim3((unsigned)blocks), dim3(kBlock), 0, s,
-                               reinterpret_cast<uint4 *>(logits), bitmask, n_words);
+            hipLaunchKernelGGL(apply_fast_kernel<true>, dim3((unsigned)blocks), dim3(kBlock), 0, s, logits, bitmask, V,
+                               W, tiles, waves, select_dense);
         else
-            hipLaunchKernelGGL(apply_fast_kernel<false>, dim3((unsigned)blocks), dim3(kBlock), 0, s,
-                               reinterpret_cast<uint4 *>(logits), bitmask, n_words);
+            hipLaunchKernelGGL(apply_fast_kernel<false>, dim3((unsigned)blocks), dim3(kBlock), 0, s, logits, bitmask,
+                               V, W, tiles, waves, select_dense);
     } else {
         const int64_t n = (int64_t)B * V;
         const int64_t blocks = std::min<int64_t>((n + kBlock - 1) / kBlock, 65536);
-        if (bf16)
-            hipLaunchKernelGGL(apply_generic_kernel<true>, dim3((unsigned)blocks), dim3(kBlock), 0, s, logits,
-                               bitmask, n, V, W);
-        else
-            hipLaunchKernelGGL(apply_generic_kernel<false>, dim3((unsigned)blocks), dim3(kBlock), 0, s, logits,
-                               bitmask, n, V, W);
+#define PSC_APPLY(BF, IX)                                                                                            \
+    hipLaunchKernelGGL((apply_generic_kernel<BF, IX>), dim3((unsigned)blocks), dim3(kBlock), 0, s, logits, bitmask,   \
+                       (IX)n, V, W)
+        // 32-bit division where the element index and the stride past it fit
+        const bool narrow = n < ((int64_t)1 << 31);
+        if (bf16 && narrow) PSC_APPLY(true, uint32_t);
+        else if (bf16) PSC_APPLY(true, int64_t);
+        else if (narrow) PSC_APPLY(false, uint32_t);
+        else PSC_APPLY(false, int64_t);
+#undef PSC_APPLY
     }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? PSC_OK : device_fail("psc_apply_mask", e);

@@ -1,0 +1,58 @@
+"""GPU parity of the masking of logits rows at every alignment: a row is cut
+at 128-byte lines of memory into 4 KiB tiles, so its first and last tile, the
+lines at their ends, lines masked whole and lines left alone are the cases;
+large batches read, select and write densely mixed tiles instead.  Compared
+bit for bit with the closed form on the same bits (the apply only copies or
+writes -inf)."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2608_03065_amd.psc import apply_mask  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _mixed_bits(B, W, seed):
+    """Runs of words all masked, all allowed, sparsely masked and dense."""
+    g = torch.Generator(DEV).manual_seed(seed)
+    word = lambda: torch.randint(-2**31, 2**31, (B, W), generator=g, device=DEV, dtype=torch.int64).to(torch.int32)
+    kind = torch.randint(0, 4, (B, (W + 6) // 7), generator=g, device=DEV).repeat_interleave(7, 1)[:, :W]
+    sparse = ~(word() & word() & word() & word())
+    return torch.where(kind == 0, 0, torch.where(kind == 1, -1, torch.where(kind == 2, sparse, word()))).int()
+
+
+def _check(B, V, dtype, offset, bits):
+    ints = torch.int16 if dtype == torch.bfloat16 else torch.int32
+    buf = torch.randint(-2**15, 2**15, (offset + B * V + 80,), device=DEV, dtype=torch.int32).to(ints)
+    want = buf.clone()
+    rows = want[offset:offset + B * V].view(B, V)
+    inf = torch.tensor(float("-inf"), dtype=dtype).view(ints).item()
+    shift = torch.arange(32, device=DEV, dtype=torch.int32)
+    for b0 in range(0, B, 8):       # in parts: the expanded bits are 4 bytes each
+        allowed = ((bits[b0:b0 + 8, :, None] >> shift) & 1).bool().flatten(1)[:, :V]
+        rows[b0:b0 + 8].masked_fill_(~allowed, inf)
+    apply_mask(buf.view(dtype)[offset:offset + B * V].view(B, V), bits)
+    torch.cuda.synchronize()
+    assert torch.equal(buf, want), (B, V, dtype, offset)   # also what lies before and after the rows
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("V", [31, 511, 512, 513, 1023, 1025, 2047, 2048, 2049, 2111, 4096, 4160, 6145])
+def test_rows_at_every_alignment(V, dtype):
+    line = 64 if dtype == torch.bfloat16 else 32
+    for offset in (0, 1, 7, line // 2, line - 1):
+        _check(line + 3, V, dtype, offset, _mixed_bits(line + 3, (V + 31) // 32, V + offset))
+
+
+@pytest.mark.parametrize("dtype,B,V,offset", [(torch.bfloat16, 28, 2000001, 5), (torch.bfloat16, 27, 2097152, 0),
+                                              (torch.float32, 27, 1050001, 3)])
+def test_large_batch_dense_and_sparse(dtype, B, V, offset):
+    """Above 104 MiB of logits: dense rows are read, selected and written,
+    sparse ones and the first and last tiles of a row are stored."""
+    W = (V + 31) // 32
+    bits = _mixed_bits(B, W, 3)
+    dense = torch.randint(-2**31, 2**31, (B // 2, W), device=DEV, dtype=torch.int64).to(torch.int32)
+    bits[:B // 2] = dense
+    _check(B, V, dtype, offset, bits)
