@@ -682,24 +682,41 @@ __device__ __forceinline__ void select_tile(__amdgpu_buffer_rsrc_t rsrc, uint32_
         __builtin_amdgcn_raw_buffer_store_b128(mask_vector<kBf16>(x[j], g[j]), rsrc, off[j], 0, kPolicyStream);
 }
 
+// The mask bits of tile t of row R, lane j < kWords those of elements 32 j ..
+// 32 j + 31 of the tile; word(w) is the row's mask word w (0 <= w < W).
+// `inside` has the bits of the elements that lie in the row (none in the other
+// lanes), and `lo` is the mask word w of which lane j is in charge (`mine`).
+template <bool kBf16>
+struct TileBits {
+    int64_t w;
+    bool mine;
+    uint32_t lo, bits, inside;
+
+    template <class Word>
+    __device__ __forceinline__ TileBits(const Row<kBf16> &R, int32_t W, int32_t t, int lane, const Word &word) {
+        using T = Tile<kBf16>;
+        w = (int64_t)t * T::kWords + lane - R.before;
+        mine = lane < T::kWords && w >= 0 && w < W;
+        uint32_t hi = 0;
+        lo = 0;
+        if (mine) lo = word((int32_t)w);
+        if (R.shift && lane < T::kWords && w >= -1 && w + 1 < W) hi = word((int32_t)w + 1);
+        bits = __builtin_amdgcn_alignbit(hi, lo, R.shift);
+        const int64_t p0 = ((int64_t)t * T::kWords + lane) * 32, left = (int64_t)R.delta + R.V - p0;
+        inside = lane < T::kWords ? ~0u : 0u;
+        if (p0 < R.delta) inside &= R.delta - p0 >= 32 ? 0u : ~0u << (R.delta - p0);
+        if (left < 32) inside &= left <= 0 ? 0u : ~(~0u << left);
+    }
+};
+
 // Mask tile t of row R: word(w) is the row's mask word w (0 <= w < W); the
 // words also go to out[0 .. W) when it is set.
 template <bool kBf16, class Word>
 __device__ __forceinline__ void mask_tile(const Row<kBf16> &R, int32_t W, int32_t t, bool select_dense, int lane,
                                           const Word &word, uint32_t *__restrict__ out) {
     using T = Tile<kBf16>;
-    // lane j < kWords: the bits of elements p0 .. p0 + 31 counted from the line
-    const int64_t w = (int64_t)t * T::kWords + lane - R.before;
-    const bool mine = lane < T::kWords && w >= 0 && w < W;
-    uint32_t lo = 0, hi = 0;
-    if (mine) lo = word((int32_t)w);
-    if (R.shift && lane < T::kWords && w >= -1 && w + 1 < W) hi = word((int32_t)w + 1);
-    uint32_t drop = ~__builtin_amdgcn_alignbit(hi, lo, R.shift);
-    // outside the row nothing is masked
-    const int64_t p0 = ((int64_t)t * T::kWords + lane) * 32, left = (int64_t)R.delta + R.V - p0;
-    if (p0 < R.delta) drop &= R.delta - p0 >= 32 ? 0u : ~0u << (R.delta - p0);
-    if (left < 32) drop &= left <= 0 ? 0u : ~(~0u << left);
-    if (lane >= T::kWords) drop = 0;
+    const TileBits<kBf16> B(R, W, t, lane, word);
+    const uint32_t drop = ~B.bits & B.inside;   // outside the row nothing is masked
     const __amdgpu_buffer_rsrc_t rsrc = wave_rsrc(R.line + (int64_t)t * kTileBytes, kTileBytes);
     constexpr uint32_t kInf = kBf16 ? kNegInf2 : kF32NegInf;
     bool select = false;
@@ -741,7 +758,7 @@ __device__ __forceinline__ void mask_tile(const Row<kBf16> &R, int32_t W, int32_
         }
     }
     // last, so that no access of the logits waits for this store
-    if (out && mine) out[w] = lo;
+    if (out && B.mine) out[B.w] = B.lo;
 }
 
 // psc_apply_mask: the tiles of the B rows, split over wavefronts.
@@ -1053,56 +1070,206 @@ __device__ __forceinline__ unsigned long long umax64(unsigned long long a, unsig
     return a > b ? a : b;
 }
 
-template <bool kBf16, bool kSliced>
-__global__ void __launch_bounds__(kFusedBlock)
+__device__ __forceinline__ unsigned long long wave_umax64(unsigned long long v) {
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) v = umax64(v, __shfl_xor(v, o, kWave));
+    return v;
+}
+
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ int dpp_max(int v) {
+    return max(v, __builtin_amdgcn_update_dpp(v, v, kCtrl, kRowMask, 0xF, false));
+}
+
+// The maximum of v over the 64 lanes of a full wavefront, uniform (the moves
+// of wave_sum; a lane that a move leaves out keeps its own value).
+__device__ __forceinline__ int wave_max(int v) {
+    v = dpp_max<0xB1, 0xF>(v);
+    v = dpp_max<0x4E, 0xF>(v);
+    v = dpp_max<0x141, 0xF>(v);
+    v = dpp_max<0x140, 0xF>(v);
+    v = dpp_max<0x142, 0xA>(v);
+    v = dpp_max<0x143, 0xC>(v);
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// The largest of three floats; a NaN wins (one instruction, v_maximum3_f32).
+__device__ __forceinline__ float maximum3(float a, uint32_t b, uint32_t c) {
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, __builtin_bit_cast(float, b)),
+                                         __builtin_bit_cast(float, c));
+}
+
+// The float bits of element k of a vector.
+template <bool kBf16>
+__device__ __forceinline__ uint32_t element(u32x4 x, int k) {
+    if (!kBf16) return x[k];
+    return (k & 1) ? x[k / 2] & 0xFFFF0000u : x[k / 2] << 16;
+}
+
+// The part of a tile of a row that one wavefront holds for the argmax.  Rows
+// are cut at 128-byte lines, as for masking, so every row alignment takes
+// 16-byte loads; the vectors at a row's ends, which may reach out of it, are
+// read element by element, one per lane.
+template <bool kBf16>
+struct ArgmaxTile {
+    using T = Tile<kBf16>;
+    static constexpr int kVecs = kTileBytes / 16 / kWave;
+    static constexpr uint32_t kFull = (1u << T::kPerVec) - 1;
+    int32_t id0;         // the token of the tile's first element
+    bool any, ends;      // wave-uniform: some token is allowed; the row starts or ends inside a vector
+    int32_t at;          // the lane's element of such a vector, in the tile
+    bool mine;           // ... and whether it is one that is allowed
+    uint32_t end_value;  // ... its float bits
+    uint32_t g[kVecs];   // allowed elements of the lane's other vectors
+    u32x4 x[kVecs];
+
+    __device__ __forceinline__ void load(const Row<kBf16> &R, int32_t t, int lane, uint32_t keep) {
+        id0 = (int32_t)((int64_t)t * T::kElems - R.delta);
+        any = __ballot(keep != 0) != 0;
+        ends = false;
+        if (!any) return;
+        const __amdgpu_buffer_rsrc_t rsrc = wave_rsrc(R.line + (int64_t)t * kTileBytes, kTileBytes);
+        // the row's first element in the tile and the one past its last
+        const int32_t begin = t ? 0 : R.delta;
+        const int32_t end = (int32_t)min((int64_t)R.delta + R.V - (int64_t)t * T::kElems, (int64_t)T::kElems);
+#pragma unroll
+        for (int j = 0; j < kVecs; j++) {
+            const int v = j * kWave + lane;
+            g[j] = (__shfl(keep, v / T::kVecsPerWord, kWave) >> ((v % T::kVecsPerWord) * T::kPerVec)) & kFull;
+            if (v * T::kPerVec < begin || (v + 1) * T::kPerVec > end) g[j] = 0;
+            x[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, g[j] != 0 ? (uint32_t)v * 16u : kOffSkip, 0, kPolicyNt);
+        }
+        ends = (begin | end) % T::kPerVec != 0;
+        if (ends) {
+            // lanes 0 .. : the vector of the first element; 32 .. : that of the end
+            const int k = lane & 31;
+            at = (lane < 32 ? begin : end) / T::kPerVec * T::kPerVec + k;
+            mine = k < T::kPerVec && at >= begin && at < end;
+            const uint32_t word = __shfl(keep, mine ? at / 32 : 0, kWave);
+            mine = mine && (word >> (at & 31) & 1);
+            const uint32_t off = mine ? (uint32_t)at * T::kElem : kOffSkip;
+            end_value = kBf16 ? (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsrc, off, 0, 0) << 16
+                              : __builtin_amdgcn_raw_buffer_load_b32(rsrc, off, 0, 0);
+        }
+    }
+
+    // The largest allowed element of vector j (a NaN if it has one).
+    __device__ __forceinline__ float top(int j) const {
+        float m = __builtin_bit_cast(float, kF32NegInf);
+        if (kBf16) {
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const uint32_t lo = (uint32_t)((int32_t)(g[j] << (31 - 2 * k)) >> 31);
+                const uint32_t hi = (uint32_t)((int32_t)(g[j] << (30 - 2 * k)) >> 31);
+                const uint32_t keep = (lo & 0xFFFFu) | (hi & 0xFFFF0000u);
+                const uint32_t d = (x[j][k] & keep) | (kNegInf2 & ~keep);
+                m = maximum3(m, d & 0xFFFF0000u, d << 16);
+            }
+        } else {
+            uint32_t d[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const uint32_t keep = (uint32_t)((int32_t)(g[j] << (31 - k)) >> 31);
+                d[k] = (x[j][k] & keep) | (kF32NegInf & ~keep);
+            }
+            m = maximum3(maximum3(m, d[0], d[1]), d[2], d[3]);
+        }
+        return m;
+    }
+};
+
+// The best (value, id) key of tiles A by one wavefront, uniform; 0 if no token
+// of them is allowed.  The kernel is bound by its instructions, not by the
+// loads, so the largest logit is found on its own first, and the place where
+// it stands once per wavefront: with a 64-bit (value, id) key per element
+// 200 x 151,665 bf16 took 25 us, at 60 MB of logits.
+template <bool kBf16, int kTiles>
+__device__ __forceinline__ unsigned long long argmax_tiles(const ArgmaxTile<kBf16> (&A)[kTiles], int lane) {
+    using T = Tile<kBf16>;
+    constexpr int kVecs = ArgmaxTile<kBf16>::kVecs;
+    float top[kTiles][kVecs], most = __builtin_bit_cast(float, kF32NegInf);
+#pragma unroll
+    for (int i = 0; i < kTiles; i++) {
+        if (!A[i].any) continue;
+#pragma unroll
+        for (int j = 0; j < kVecs; j++) top[i][j] = A[i].top(j);
+        most = maximum3(most, __builtin_bit_cast(uint32_t, __builtin_elementwise_maximum(top[i][0], top[i][1])),
+                        __builtin_bit_cast(uint32_t, __builtin_elementwise_maximum(top[i][2], top[i][3])));
+    }
+    static_assert(kVecs == 4, "the vectors of a tile");
+    const bool nan = __ballot(most != most) != 0;
+    // the largest of the wavefront: as integers of the same order, -0 = +0
+    const int32_t bits = __builtin_bit_cast(int32_t, most), sign = bits >> 31;
+    const int32_t all = wave_max(((bits & 0x7FFFFFFF) ^ sign) - sign);
+    most = __builtin_bit_cast(float, all < 0 ? (uint32_t)-all | 0x80000000u : (uint32_t)all);
+    unsigned long long key = 0;
+    // the first vector that has it (in id order), then its first element
+#pragma unroll
+    for (int i = 0; i < kTiles; i++) {
+        if (!A[i].any) continue;
+#pragma unroll
+        for (int j = 0; j < kVecs; j++) {
+            if (key) continue;
+            const unsigned long long in =
+                __ballot(A[i].g[j] != 0 && (nan ? top[i][j] != top[i][j] : top[i][j] == most));
+            if (!in) continue;
+            const int l = __ffsll((long long)in) - 1;
+            int first = 0;
+            uint32_t value = 0;
+#pragma unroll
+            for (int k = T::kPerVec - 1; k >= 0; k--) {
+                const uint32_t u = element<kBf16>(A[i].x[j], k);
+                const float f = __builtin_bit_cast(float, u);
+                const bool hit = ((A[i].g[j] >> k) & 1) && (nan ? f != f : f == most);
+                first = hit ? k : first;
+                value = hit ? u : value;
+            }
+            first = __builtin_amdgcn_readlane(first, l);
+            value = (uint32_t)__builtin_amdgcn_readlane((int)value, l);
+            key = arg_key(value, A[i].id0 + (j * kWave + l) * T::kPerVec + first);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kTiles; i++)
+        if (A[i].ends) key = umax64(key, wave_umax64(A[i].mine ? arg_key(A[i].end_value, A[i].id0 + A[i].at) : 0));
+    return key;
+}
+
+template <bool kBf16, bool kSliced, int kTiles>
+__global__ void __launch_bounds__(kFusedBlock, kTiles == 1 ? 7 : 5)
 argmax_partial_kernel(const int32_t *__restrict__ table, const uint32_t *__restrict__ masks, int32_t mask_stride,
                       const int32_t *__restrict__ ids, int32_t n_lex, int32_t n_lr,
                       const int32_t *__restrict__ stacks, int32_t stride, int64_t n_stack,
                       const int32_t *__restrict__ lens, const int32_t *__restrict__ qs, int32_t V, int32_t W,
                       uint32_t *__restrict__ err, const void *__restrict__ logits, int32_t fast,
-                      unsigned long long *__restrict__ records, int32_t *__restrict__ out_tokens) {
-    using G = ApplyGeom<kBf16>;
+                      int32_t per_wave, unsigned long long *__restrict__ records, int32_t *__restrict__ out_tokens) {
     __shared__ unsigned long long s_best[kFusedBlock / kWave];
     const int b = blockIdx.y;
+    const Row<kBf16> R(const_cast<void *>(logits), b, V);
     const int cls = block_class(table, n_lex, n_lr, stacks, stride, n_stack, lens, qs, b, err);
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     unsigned long long best = 0;   // every real key is > 0
     if (cls >= 0) {
         if (fast) {
-            // the apply's layout: the wavefront's kWordsPerWave words, lane j
-            // the vectors j, j + 64, ...; only vectors with an allowed token are read
-            constexpr uint32_t kFull = (1u << G::kPerVec) - 1;
-            const int w0 = (blockIdx.x * (kFusedBlock / kWave) + wave) * G::kWordsPerWave;
-            if (w0 < W) {
-                const uint4 *row = reinterpret_cast<const uint4 *>(logits) + ((size_t)b * W + w0) * G::kVecsPerWord;
-                const uint32_t m =
-                    lane < G::kWordsPerWave && w0 + lane < W ? *mask_at<kSliced>(masks, mask_stride, ids, cls, w0 + lane)
-                                                             : 0u;
-                uint32_t g[G::kVecs];
-                uint4 x[G::kVecs];
+            const auto word = [&](int32_t w) { return *mask_at<kSliced>(masks, mask_stride, ids, cls, w); };
+            const int32_t t0 = (blockIdx.x * (kFusedBlock / kWave) + wave) * per_wave;
+            for (int32_t t = t0; t < t0 + per_wave; t += kTiles) {
+                int l = lane;   // of this turn only: what is derived from it need not be held over the turns
+                asm volatile("" : "+v"(l));
+                ArgmaxTile<kBf16> A[kTiles];
+                uint32_t keep[kTiles];
 #pragma unroll
-                for (int j = 0; j < G::kVecs; j++) {
-                    const int v = j * kWave + lane;
-                    g[j] = (__shfl(m, v / G::kVecsPerWord, kWave) >> ((v % G::kVecsPerWord) * G::kPerVec)) & kFull;
+                for (int i = 0; i < kTiles; i++) {
+                    const TileBits<kBf16> K(R, W, t + i, l, word);
+                    keep[i] = K.bits & K.inside;
                 }
 #pragma unroll
-                for (int j = 0; j < G::kVecs; j++)
-                    if (g[j]) x[j] = load_nt(row + j * kWave + lane);
-#pragma unroll
-                for (int j = 0; j < G::kVecs; j++) {
-                    if (!g[j]) continue;
-                    const uint32_t *e = reinterpret_cast<const uint32_t *>(&x[j]);
-                    const int v0 = (w0 * G::kVecsPerWord + j * kWave + lane) * G::kPerVec;
-#pragma unroll
-                    for (int k = 0; k < G::kPerVec; k++) {
-                        if (!((g[j] >> k) & 1)) continue;
-                        const uint32_t f = kBf16 ? ((k & 1) ? (e[k / 2] & 0xFFFF0000u) : (e[k / 2] << 16)) : e[k];
-                        best = umax64(best, arg_key(f, v0 + k));
-                    }
-                }
+                for (int i = 0; i < kTiles; i++) A[i].load(R, t + i, l, keep[i]);
+                best = umax64(best, argmax_tiles<kBf16, kTiles>(A, l));
             }
         } else {
-            const int v_end = min(V, (blockIdx.x + 1) * kGenWords * 32);
+            // logits that are not at their elements' own alignment
+            const int v_end = (int)min((int64_t)V, ((int64_t)blockIdx.x + 1) * kGenWords * 32);
             for (int v = blockIdx.x * kGenWords * 32 + threadIdx.x; v < v_end; v += kFusedBlock) {
                 if (!((*mask_at<kSliced>(masks, mask_stride, ids, cls, v >> 5) >> (v & 31)) & 1u)) continue;
                 const size_t idx = (size_t)b * V + v;
@@ -1110,19 +1277,21 @@ argmax_partial_kernel(const int32_t *__restrict__ table, const uint32_t *__restr
                                          : reinterpret_cast<const uint32_t *>(logits)[idx];
                 best = umax64(best, arg_key(f, v));
             }
+            best = wave_umax64(best);
         }
     }
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) best = umax64(best, __shfl_xor(best, o, kWave));
     if (lane == 0) s_best[wave] = best;
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int k = 1; k < kFusedBlock / kWave; k++) best = umax64(best, s_best[k]);
         unsigned long long *slot = records + (size_t)b * kArgmaxRecordWords;
         uint32_t *arrivals = reinterpret_cast<uint32_t *>(slot + 1);
-        const unsigned long long seen = __hip_atomic_fetch_max(slot, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // the max has been performed once its old value is back
-        asm volatile("s_waitcnt vmcnt(0)" ::"v"((uint32_t)seen) : "memory");
+        if (best) {
+            const unsigned long long seen =
+                __hip_atomic_fetch_max(slot, best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // the max has been performed once its old value is back
+            asm volatile("s_waitcnt vmcnt(0)" ::"v"((uint32_t)seen) : "memory");
+        }
         const uint32_t arrived = __hip_atomic_fetch_add(arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (arrived == gridDim.x - 1) {
             const unsigned long long k = __hip_atomic_exchange(slot, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1669,6 +1838,34 @@ psc_status launch_fused(const psc_handle *h, const int32_t *stacks, int32_t stri
     return launched(what);
 }
 
+// Compute units of the current GPU.
+int compute_units() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+    return cus;
+}
+
+// Tiles of a row that one wavefront of the argmax takes (two at a time where
+// more than one): one where that gives at most 4 workgroups per compute unit,
+// otherwise as many as it takes for all workgroups to be on the GPU at once, 5
+// per compute unit (the pair's registers), since each begins with its
+// sequence's walk and ends with two atomics.  us, 1 / 2 / 4 / 8 tiles a
+// wavefront: 8 x 32,000 bf16 (32 workgroups of one tile) 7.1 / 8.0 / 10.4 / 15.3;
+// 64 x 151,936 (1,216) 11.5 / 11.1 / 13.6 / 18.7; 128 x 151,936 (2,432) 11.6 /
+// 10.2 / 13.5 / 18.9; 200 x 151,665 (3,800) 23.1 / 21.1 / 18.4 / 24.0;
+// 256 x 262,144 (8,192) 43.1 / 37.9 / 32.9 / 30.2.
+int32_t argmax_tiles_per_wave(int32_t tiles, int32_t B) {
+    const int64_t cus = compute_units();
+    const int32_t waves = kFusedBlock / kWave;
+    auto blocks = [&](int32_t per) { return (int64_t)((tiles + (int64_t)waves * per - 1) / ((int64_t)waves * per)) * B; };
+    if (blocks(1) <= 4 * cus) return 1;
+    int32_t per = 2;
+    while (blocks(per) > 5 * cus && waves * per < tiles) per *= 2;
+    return per;
+}
+
 // The masked argmax for ragged (stride 0) or strided stacks.
 // `records` is the per-sequence slot array (kArgmaxRecordWords uint64 per
 // sequence, zero between calls); null selects the bound buffer's.
@@ -1683,20 +1880,29 @@ psc_status launch_argmax(const psc_handle *h, const int32_t *stacks, int32_t str
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     char *base = static_cast<char *>(h->dev_base);
     const Bound T = bound(h);
-    const int fast = (V % 32 == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15) == 0);
+    const bool bf16 = dtype == PSC_BF16;
+    const int fast = vector_path(logits, bf16);
     const int32_t W = h->W;
-    const int words_per_block = !fast ? kGenWords : fused_words_per_block(dtype == PSC_BF16);
-    dim3 grid((W + words_per_block - 1) / words_per_block, B);
+    const int32_t waves = kFusedBlock / kWave;
+    const int32_t tiles = tiles_of(logits, bf16, V);
+    const int32_t per_wave = fast ? argmax_tiles_per_wave(tiles, B) : 1;
+    dim3 grid(fast ? (tiles + waves * per_wave - 1) / (waves * per_wave) : (W + kGenWords - 1) / kGenWords, B);
     if (!records) records = reinterpret_cast<unsigned long long *>(base + h->argmax_off);
+#define PSC_ARGMAX_N(BF, SL, NT)                                                                                     \
+    hipLaunchKernelGGL((argmax_partial_kernel<BF, SL, NT>), grid, dim3(kFusedBlock), 0, s, T.table, T.masks,          \
+                       T.mstride, T.ids, h->n_lex, h->n_lr, stacks, stride, n_stack, stack_lens, lexer_states, V, W, \
+                       T.err, logits, fast, per_wave, records, out_tokens)
 #define PSC_ARGMAX(BF, SL)                                                                                           \
-    hipLaunchKernelGGL((argmax_partial_kernel<BF, SL>), grid, dim3(kFusedBlock), 0, s, T.table, T.masks, T.mstride,   \
-                       T.ids, h->n_lex, h->n_lr, stacks, stride, n_stack, stack_lens, lexer_states, V, W, T.err,    \
-                       logits, fast, records, out_tokens)
-    if (dtype == PSC_BF16 && T.sliced) PSC_ARGMAX(true, true);
-    else if (dtype == PSC_BF16) PSC_ARGMAX(true, false);
+    do {                                                                                                             \
+        if (per_wave > 1) PSC_ARGMAX_N(BF, SL, 2);                                                                   \
+        else PSC_ARGMAX_N(BF, SL, 1);                                                                                \
+    } while (0)
+    if (bf16 && T.sliced) PSC_ARGMAX(true, true);
+    else if (bf16) PSC_ARGMAX(true, false);
     else if (T.sliced) PSC_ARGMAX(false, true);
     else PSC_ARGMAX(false, false);
 #undef PSC_ARGMAX
+#undef PSC_ARGMAX_N
     return launched(what);
 }
 
@@ -1752,13 +1958,7 @@ AdvTables adv_tables(const psc_handle *h) {
 // Workgroups of 256 threads that fit on the current GPU at once: 8 per
 // compute unit (4 SIMDs x 8 wavefronts; the fused kernels' registers allow
 // it), from the device's compute-unit count.
-int64_t resident_blocks() {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        cus = 256;
-    return (int64_t)cus * 8;
-}
+int64_t resident_blocks() { return (int64_t)compute_units() * 8; }
 
 bool ranges_overlap(const void *a, const void *b, size_t n) {
     const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);

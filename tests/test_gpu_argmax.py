@@ -175,3 +175,38 @@ def test_argmax_graph_replays(built):
         torch.cuda.synchronize()
         assert torch.equal(g_out, eager), rep
         assert np.array_equal(g_out.cpu().numpy(), _closed_form(logits, want_bits, wl.V)), rep
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("V", [33, 511, 2047, 2049, 4095, 4160, 6145])
+def test_argmax_rows_at_every_alignment(V, dtype):
+    """Odd rows start at every alignment: the largest allowed logit (and a tie
+    of it, later) at the first and last allowed token, at the edges of 16-byte
+    vectors, 128-byte lines and 4 KiB tiles; disallowed and foreign neighbours
+    are larger.  The result is a token id: compared exactly."""
+    class Vocab:
+        tokens = [b"%d" % (10 + i) if i % 3 else b"x%d" % i for i in range(V - 1)] + [b""]
+        eos_id = V - 1
+    clf = psc.Classifier.from_text('%start v\nN: /[0-9]+/\nS: /"[a-z0-9]*"/\nv: N | S\n', Vocab).bind(DEV)
+    line = 64 if dtype == torch.bfloat16 else 32
+    B = line + 3
+    states = [clf.host_state(b'"' if b % 2 else b"") for b in range(B)]
+    bits = clf.masks_host(states)
+    rng = np.random.default_rng(V)
+    for offset, shift in ((0, 0), (1, 3), (line - 1, 0)):
+        x = rng.standard_normal((B, V)).astype(np.float32) - (8 if offset else 0)
+        for b in range(B):
+            allowed = np.unpackbits(bits[b].astype("<u4").view(np.uint8), bitorder="little")[:V].astype(bool)
+            x[b, ~allowed] = 50
+            ids = np.nonzero(allowed)[0]
+            edge = ((offset + b * V) % line + ids) % (line if b % 3 else 32 * line)
+            near = ids[(edge < 2) | (edge >= edge.max() - 1)]
+            pick = rng.choice(near, 2) if b % 4 else ids[[0, -1]]
+            x[b, pick] = np.float32("nan") if b % 11 == 5 else np.float32("-inf") if b % 13 == 7 else 1e-40 if b % 17 == 3 else 20 - shift * 20
+        x = torch.from_numpy(x).to(dtype)
+        buf = torch.full((offset + B * V + 64,), 99.0, dtype=dtype, device=DEV)
+        dev = buf[offset:offset + B * V].view(B, V)
+        dev.copy_(x.to(DEV))
+        got = clf.compute_and_argmax(*pack_states(states, DEV), dev).cpu().numpy()
+        want = _closed_form(x, bits, V)
+        assert np.array_equal(got, want), (offset, np.nonzero(got != want)[0][:5])
