@@ -937,7 +937,9 @@ DeviceLayout device_layout(const psc_handle &h, uint32_t flags) {
     L.vbytes = L.gram + up(h.gram.size() * sizeof(int32_t));
     L.argmax = L.vbytes + up(h.vbytes.size());
     L.packed = L.argmax + kArgmaxBytes;
-    L.closure = L.packed + up((size_t)h.n_lr * h.adv.n_term * sizeof(int32_t));
+    L.records = L.packed + up((size_t)h.n_lr * h.adv.n_term * sizeof(int32_t));
+    L.steps = L.records + up((size_t)h.V * kTokenInts * sizeof(int32_t));
+    L.closure = L.steps + up(lexer_steps_bytes(h));
     L.pred = L.closure + up(goto_closure_bytes(h));
     L.total = L.pred + up((size_t)start_block_count(h.n_lex) * kPredInts * sizeof(int32_t));
     return L;
@@ -1001,22 +1003,22 @@ bool packed_action(const psc_handle &h, std::vector<int32_t> &out) {
 }
 
 size_t goto_closure_bytes(const psc_handle &h) {
-    const size_t n = (size_t)h.n_lr * h.adv.n_nt * h.adv.n_term * sizeof(int32_t);
-    return n <= kClosureMaxBytes ? n : 0;
+    const size_t n = (size_t)h.n_lr * h.adv.n_nt * h.adv.n_term;
+    return n <= kClosureMaxEntries ? n * 2 * sizeof(int32_t) : 0;
 }
 
-void goto_closure(const psc_handle &h, std::vector<int32_t> &out) {
+void goto_closure(const psc_handle &h, const int32_t *action, std::vector<int32_t> &out) {
     out.clear();
     if (!goto_closure_bytes(h)) return;
     const AdvanceLayout &L = h.adv;
     const int32_t *act = h.gram.data() + L.action, *go = h.gram.data() + L.go,
                   *lhs = h.gram.data() + L.prod_lhs, *len = h.gram.data() + L.prod_len;
     const int64_t nt = L.n_nt, nT = L.n_term;
-    out.assign((size_t)h.n_lr * nt * nT, -1);
+    out.assign((size_t)h.n_lr * nt * nT * 2, -1);
     for (int64_t s = 0; s < h.n_lr; s++)
         for (int64_t A = 0; A < nt; A++) {
             const int32_t g0 = go[s * nt + A];
-            int32_t *row = out.data() + (s * nt + A) * nT;
+            int32_t *row = out.data() + (s * nt + A) * nT * 2;
             if (g0 < 0) continue;
             for (int64_t t = 0; t < nT; t++) {
                 int32_t x = g0;
@@ -1028,7 +1030,49 @@ void goto_closure(const psc_handle &h, std::vector<int32_t> &out) {
                     x = go[s * nt + lhs[a >> 2]];
                     if (x < 0) break;
                 }
-                row[t] = x;
+                row[2 * t] = x;
+                if (x >= 0) row[2 * t + 1] = action[(int64_t)x * nT + t];
+            }
+        }
+}
+
+void token_records(const psc_handle &h, std::vector<int32_t> &out) {
+    const int32_t *off = h.gram.data() + h.adv.tok_off;
+    out.assign((size_t)h.V * kTokenInts, 0);
+    for (int32_t t = 0; t < h.V; t++) {
+        int32_t *r = out.data() + (size_t)t * kTokenInts;
+        r[0] = off[t];
+        r[1] = off[t + 1] - off[t];
+        for (int32_t i = 0; i < r[1] && i < kTokenBytes; i++)
+            r[2 + i / 4] |= (int32_t)((uint32_t)h.vbytes[(size_t)off[t] + i] << (8 * (i % 4)));
+    }
+}
+
+bool lexer_steps_wide(const psc_handle &h) { return h.n_lex > 0xFFFE || h.adv.n_term > 0xFFFE; }
+
+size_t lexer_steps_bytes(const psc_handle &h) {
+    return (size_t)h.n_lex * 256 * (lexer_steps_wide(h) ? 2 : 1) * sizeof(int32_t);
+}
+
+void lexer_steps(const psc_handle &h, std::vector<int32_t> &out) {
+    const int32_t *next = h.gram.data() + h.adv.lex_next, *accept = h.gram.data() + h.adv.lex_accept,
+                  *ignored = h.gram.data() + h.adv.ignored;
+    const bool wide = lexer_steps_wide(h);
+    out.assign(lexer_steps_bytes(h) / sizeof(int32_t), 0);
+    for (int64_t q = 0; q < h.n_lex; q++)
+        for (int64_t c = 0; c < 256; c++) {
+            int32_t to = next[q * 256 + c], t = -1;
+            if (to < 0) {
+                t = q != 0 ? accept[q] : -1;
+                to = t < 0 || next[c] < 0 ? -1 : next[c];
+                if (t >= 0 && ignored[t]) t = -1;
+            }
+            const size_t i = (size_t)(q * 256 + c);
+            if (wide) {
+                out[2 * i] = to;
+                out[2 * i + 1] = t;
+            } else {
+                out[i] = (int32_t)((uint32_t)(to + 1) | (uint32_t)(t + 1) << 16);
             }
         }
 }

@@ -56,6 +56,7 @@ __device__ __forceinline__ int64_t wave_sum(int64_t v) {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 
 // Streaming (non-temporal) 16-byte accesses: the logits and mask rows are
 // touched once per step, so they should not evict the classifier table.
@@ -1322,11 +1323,15 @@ zero_words_kernel(unsigned long long *__restrict__ p, int64_t n) {
 // The problem instance on the device (the lexing and parsing steps of
 // Algorithm 2, which turn a prefix state and a token into the next state).
 struct AdvTables {
-    const int32_t *lex_next, *lex_accept, *ignored, *action, *go, *prod_lhs, *prod_len, *tok_off;
+    const int32_t *lex_accept, *ignored, *action, *go, *prod_lhs, *prod_len;
+    const int32_t *tokens;      // [V][kTokenInts] spellings (token_records)
     const uint8_t *bytes;
+    const void *steps;          // the lexer's byte steps (lexer_steps)
     int32_t n_lex, n_lr, n_term, n_nt, end_term, eos, V;
     int32_t packed;    // action holds packed reductions (kind | len << 2 | lhs << 10)
-    const int32_t *closure;   // GOTO with the following unit reductions done, or null
+    int32_t wide;      // steps holds pairs, not packed entries
+    const i32x2 *closure;   // GOTO with the following unit reductions done and the action on it, or null
+    bool plain() const { return packed && closure && !wide; }
 };
 
 constexpr int kOverlay = 192;          // states one token may push above what it keeps
@@ -1341,22 +1346,48 @@ __device__ __forceinline__ int64_t feed_step_bound(int32_t n_nt, int len, int ca
 }
 
 // One wavefront advances one sequence by one token.  Everything it computes
-// is uniform across the wavefront (the sequence is the workgroup's), so the
-// table reads are scalar loads with one address each, and no sequence waits
-// for another's path through the lexer and the parser.  The token's bytes
-// are fetched up front, 64 at a time, one per lane.  While the token is
-// processed the kept part of the stack, stacks[b][0 .. ptr), is only read
-// and the states pushed above it live in an LDS overlay, so a rejected token
-// leaves the stack, its length and the lexer state exactly as they were; on
-// success the overlay is written above ptr.  A terminal is fed as the LR
-// parser does: the reductions its lookahead selects, then a shift (accept
-// for $end); popping the whole stack or a missing goto rejects.
+// is uniform across the wavefront (the sequence is the workgroup's), so no
+// sequence waits for another's path through the lexer and the parser.  While
+// the token is processed the kept part of the stack, stacks[b][0 .. ptr), is
+// only read and the states pushed above it live in an LDS overlay, so a
+// rejected token leaves the stack, its length and the lexer state exactly as
+// they were; on success the overlay is written above ptr.  A terminal is fed
+// as the LR parser does: the reductions its lookahead selects, then a shift
+// (accept for $end); popping the whole stack or a missing goto rejects.
+//
+// The step is a chain: dependent loads, 0.1 us each, and the instructions
+// between them, which one wavefront issues alone and fetches for the first
+// time.  So the loads are few and the code is short:
+//   1  the token, the stack's length, the lexer state;
+//   2  the token's record (length and first bytes) and the top 64 symbols of
+//      the stack, one per lane, so that pops above them load nothing;
+//   3+ one load per byte (the next state, and the terminal that the byte
+//      ends), one per terminal (its action on the state on top), one per
+//      reduction (the state pushed and its action on the lookahead).
+// The tables are read through uniform(): scalar loads.  One token of each of
+// 128 sequences of a programming language: 5.0 us, against 6.1 with the offset,
+// the bytes, the accepting terminal and each GOTO and action read one after the
+// other; eight decoding steps of 64 x 128,256 bf16 89 against 94.  Lexing 8 or
+// 16 bytes at once, from their columns of the lexer's table in registers, was
+// no faster (5.3 and 5.2): the unrolled code took what the loads no longer did.
 //
 // advance_core computes the outcome of token `tok` on the state (q_in, st
 // of `len` symbols, at most `cap`) and writes nothing but the overlay: on
 // PSC_ADV_OK the new state is st[0 .. ptr) followed by s_ov[0 .. ov), in
 // lexer state q; on any other status the state is unchanged (ptr = len,
-// ov = 0, q = q_in).
+// ov = 0, q = q_in).  tok, len and q_in are wave-uniform.
+static_assert((kTokenInts & (kTokenInts - 1)) == 0 && kTokenInts <= kWave, "the lanes read a record at once");
+
+// *p by a scalar load: p is wave-uniform, and what it points to is not written
+// while the kernel runs.
+template <class V>
+__device__ __forceinline__ V uniform(const V *p) {
+    return *reinterpret_cast<const V __attribute__((address_space(4))) *>(reinterpret_cast<uintptr_t>(p));
+}
+
+// kPlain: the tables have the forms that nearly all grammars get (packed
+// reductions, the closure, packed lexer steps); the others are chosen by T.
+template <bool kPlain>
 __device__ __forceinline__ int advance_core(const AdvTables &T, int32_t *s_ov, const int32_t *__restrict__ st,
                                             int len, int q_in, int tok, int cap, int lane, int &ptr_out,
                                             int &ov_out, int &q_out) {
@@ -1365,93 +1396,108 @@ __device__ __forceinline__ int advance_core(const AdvTables &T, int32_t *s_ov, c
     q_out = q_in;
     if (tok < 0) return PSC_ADV_SKIPPED;
     if (tok >= T.V || len < 1 || len > cap || q_in < 0 || q_in >= T.n_lex) return PSC_ADV_BAD_INPUT;
+    int win = st[max(len - 1 - lane, 0)];
+    int rec = T.tokens[(int64_t)tok * kTokenInts + (lane & (kTokenInts - 1))];
+    // both loads are issued before either is waited for
+    asm volatile("" : "+v"(win), "+v"(rec));
     int ptr = len, ov = 0;
-    int32_t cur = st[ptr - 1];   // the top of the stack, kept in a register
-    auto reload = [&]() { cur = __builtin_amdgcn_readfirstlane(ov > 0 ? s_ov[ov - 1] : st[ptr - 1]); };
-    auto push = [&](int32_t x) {
-        if (ov >= kOverlay) return false;
-        s_ov[ov++] = x;          // every lane writes the same value
-        cur = x;
-        return true;
-    };
-    // states come from the tables (validated when built) or, below the
-    // overlay, from the caller's stack, which is checked before each use
-    const int64_t max_steps = feed_step_bound(T.n_nt, len, cap);
+    int32_t cur = __builtin_amdgcn_readlane(win, 0);   // the top of the stack, kept in a register
+    const uint32_t n_lr = (uint32_t)T.n_lr;
+    // feed terminal t: states come from the tables (validated when built) or,
+    // below the overlay, from the caller's stack, which is checked before use
+    const int max_steps = (int)min(feed_step_bound(T.n_nt, len, cap), (int64_t)INT32_MAX);
     auto feed = [&](int32_t t) -> int {
-        for (int64_t guard = 0; guard < max_steps; guard++) {
-            const int32_t s0 = cur;
-            if (s0 < 0 || s0 >= T.n_lr) return PSC_ADV_BAD_INPUT;
-            const int32_t a = T.action[(int64_t)s0 * T.n_term + t];
-            const int kind = a & 3;
-            if (kind == 1) return push(a >> 2) ? PSC_ADV_OK : PSC_ADV_OVERFLOW;
-            if (kind == 3) return PSC_ADV_OK;
-            if (kind == 0) return PSC_ADV_REJECTED;
-            int32_t lhs;
-            int k;
-            if (T.packed) {
-                lhs = a >> 10;
-                k = (a >> 2) & 255;
-            } else {
-                const int32_t p = a >> 2;
-                lhs = T.prod_lhs[p];
-                k = T.prod_len[p];
+        if ((uint32_t)cur >= n_lr) return PSC_ADV_BAD_INPUT;
+        int32_t a = uniform(T.action + ((int64_t)cur * T.n_term + t));
+        int left = max_steps;
+        while ((a & 3) == 2) {
+            int32_t lhs = a >> 10, k = (a >> 2) & 255;
+            if (!kPlain && !T.packed) {
+                lhs = uniform(T.prod_lhs + (a >> 2));
+                k = uniform(T.prod_len + (a >> 2));
             }
             const int from_ov = min(k, ov);
             ov -= from_ov;
             k -= from_ov;
-            if (k >= ptr) return PSC_ADV_REJECTED;       // nothing left to goto from
+            if (k >= ptr || --left < 0) return PSC_ADV_REJECTED;       // nothing left to goto from
             ptr -= k;
-            reload();
-            const int32_t s1 = cur;
-            if (s1 < 0 || s1 >= T.n_lr) return PSC_ADV_BAD_INPUT;
+            const int down = len - ptr;
+            if (ov > 0) cur = __builtin_amdgcn_readfirstlane(s_ov[ov - 1]);
+            else cur = __builtin_amdgcn_readlane(win, down & (kWave - 1));
+            if (ov == 0 && down >= kWave) cur = __builtin_amdgcn_readfirstlane(st[ptr - 1]);
+            if ((uint32_t)cur >= n_lr) return PSC_ADV_BAD_INPUT;
             // with the closure, the unit reductions the lookahead selects
             // next are done here too (each would pop the state just pushed
-            // and push a GOTO from s1): the stack ends the same
-            const int32_t g = T.closure ? T.closure[((int64_t)s1 * T.n_nt + lhs) * T.n_term + t]
-                                        : T.go[(int64_t)s1 * T.n_nt + lhs];
-            if (g < 0) return PSC_ADV_REJECTED;
-            if (!push(g)) return PSC_ADV_OVERFLOW;
+            // and push a GOTO from cur): the stack ends the same
+            if (kPlain || T.closure) {
+                // (32 bits: the closure has at most kClosureMaxEntries)
+                const i32x2 e = uniform(T.closure + (((uint32_t)cur * T.n_nt + lhs) * T.n_term + t));
+                cur = e.x;
+                a = e.y;
+            } else {
+                cur = uniform(T.go + ((int64_t)cur * T.n_nt + lhs));
+                if (cur >= 0) a = uniform(T.action + ((int64_t)cur * T.n_term + t));
+            }
+            if (cur < 0) return PSC_ADV_REJECTED;
+            if (ov >= kOverlay) return PSC_ADV_OVERFLOW;
+            s_ov[ov++] = cur;          // every lane writes the same value
         }
-        return PSC_ADV_REJECTED;
+        if ((a & 3) == 1) {
+            if (ov >= kOverlay) return PSC_ADV_OVERFLOW;
+            cur = a >> 2;
+            s_ov[ov++] = cur;
+        }
+        return (a & 3) == 0 ? PSC_ADV_REJECTED : PSC_ADV_OK;
     };
     int q = q_in, res = PSC_ADV_OK;
-    if (tok == T.eos) {
-        // the pending lexeme becomes its terminal, then $end must be accepted
-        res = PSC_ADV_EOS;
-        if (q != 0) {
-            const int32_t t = T.lex_accept[q];
-            if (t < 0) res = PSC_ADV_REJECTED;
-            else if (!T.ignored[t]) {
-                const int r = feed(t);
-                if (r != PSC_ADV_OK) res = r;
-            }
+    const bool eos = tok == T.eos;
+    const int at = __builtin_amdgcn_readlane(rec, 0), n = eos ? 2 : __builtin_amdgcn_readlane(rec, 1);
+    int base = 0;   // the byte that lane 2's int of `rec` starts at
+    for (int i = 0; i < n; i++) {
+        int next = 0, term = -1;   // where a byte leads (-1: nowhere), the terminal it ends (-1: none)
+        if (!eos) {
+            // longest match with one byte of lookahead: a byte the pending lexeme
+            // cannot take ends it (it must be accepting) and starts the next from q0
+            do {
+                if (i - base == kTokenBytes) {
+                    // past the record: the next bytes from the vocabulary, four per int
+                    // (the last of them may be past its end, but not past the bound buffer's)
+                    base = i;
+                    const int from = base + 4 * (lane - 2);
+                    rec = 0;
+                    if (lane >= 2 && lane < kTokenInts && from < n) __builtin_memcpy(&rec, T.bytes + at + from, 4);
+                }
+                const uint32_t four = (uint32_t)__builtin_amdgcn_readlane(rec, 2 + ((i - base) >> 2));
+                const int c = (int)(four >> (8 * ((i - base) & 3)) & 255u);
+                if (kPlain || !T.wide) {
+                    const uint32_t e = uniform(static_cast<const uint32_t *>(T.steps) + (uint32_t)(q * 256 + c));
+                    next = (int)(e & 0xFFFFu) - 1;
+                    term = (int)(e >> 16) - 1;
+                } else {
+                    const i32x2 e = uniform(static_cast<const i32x2 *>(T.steps) + ((int64_t)q * 256 + c));
+                    next = e.x;
+                    term = e.y;
+                }
+                q = next;
+            } while ((next | ~term) >= 0 && ++i < n);   // on while it leads somewhere and ends nothing
+        } else if (i == 1) {
+            // the pending lexeme became its terminal; $end must be accepted
+            term = T.end_term;
+        } else if (q != 0) {
+            term = uniform(T.lex_accept + q);
+            if (term < 0) next = -1;
+            else if (uniform(T.ignored + term)) term = -1;
         }
-        if (res == PSC_ADV_EOS) {
-            const int r = feed(T.end_term);
-            if (r != PSC_ADV_OK) res = r;
+        if (term >= 0) {
+            res = feed(term);
+            if (res != PSC_ADV_OK) break;
         }
-        return res;
+        if (next < 0) {
+            res = PSC_ADV_REJECTED;
+            break;
+        }
     }
-    // longest match with one byte of lookahead: a byte the pending lexeme
-    // cannot take ends it (it must be accepting) and starts the next from q0
-    const int i0 = T.tok_off[tok], n = T.tok_off[tok + 1] - i0;
-    for (int base = 0; base < n && res == PSC_ADV_OK; base += kWave) {
-        const int chunk = __builtin_amdgcn_readfirstlane(min(kWave, n - base));
-        const int byte = lane < chunk ? T.bytes[i0 + base + lane] : 0;
-        for (int j = 0; j < chunk; j++) {
-            const int c = __builtin_amdgcn_readlane(byte, j);
-            const int32_t nx = T.lex_next[(int64_t)q * 256 + c];
-            if (nx >= 0) { q = nx; continue; }
-            const int32_t t = q != 0 ? T.lex_accept[q] : -1;
-            if (t < 0) { res = PSC_ADV_REJECTED; break; }
-            if (!T.ignored[t]) {
-                res = feed(t);
-                if (res != PSC_ADV_OK) break;
-            }
-            q = T.lex_next[c];
-            if (q < 0) { res = PSC_ADV_REJECTED; break; }
-        }
-    }
+    if (eos) return res == PSC_ADV_OK ? PSC_ADV_EOS : res;
     if (res == PSC_ADV_OK && ptr + ov > cap) res = PSC_ADV_OVERFLOW;
     if (res == PSC_ADV_OK) {
         ptr_out = ptr;
@@ -1461,8 +1507,16 @@ __device__ __forceinline__ int advance_core(const AdvTables &T, int32_t *s_ov, c
     return res;
 }
 
+// The kernel arguments that the advance needs, all fetched at its start: left
+// to the places that use them they are five more round trips in a row.
+__device__ __forceinline__ void hold(const AdvTables &T) {
+    asm volatile("" ::"s"(T.lex_accept), "s"(T.action), "s"(T.tokens), "s"(T.steps), "s"(T.closure), "s"(T.n_lex),
+                 "s"(T.n_lr), "s"(T.n_term), "s"(T.n_nt), "s"(T.eos), "s"(T.V), "s"(T.packed), "s"(T.wide));
+}
+
 // psc_advance: one workgroup of one wavefront per sequence, the state
 // updated in place.
+template <bool kPlain>
 __global__ void __launch_bounds__(kWave)
 advance_kernel(AdvTables T, int32_t *__restrict__ stacks, int32_t cap, int32_t *__restrict__ lens,
                int32_t *__restrict__ qs, int32_t B, const int32_t *__restrict__ tokens,
@@ -1470,10 +1524,12 @@ advance_kernel(AdvTables T, int32_t *__restrict__ stacks, int32_t cap, int32_t *
     __shared__ int32_t s_ov[kOverlay];
     const int b = blockIdx.x;
     const int lane = threadIdx.x;
-    const int tok = tokens[b];
-    const int len = tok < 0 ? 0 : lens[b], q_in = tok < 0 ? 0 : qs[b];
+    // one round trip: nothing of a skipped sequence's state is used
+    hold(T);
+    int tok = uniform(tokens + b), len = uniform(lens + b), q_in = uniform(qs + b);
+    asm volatile("" : "+s"(tok), "+s"(len), "+s"(q_in));   // held, not read again: the state is written below
     int ptr, ov, q;
-    const int res = advance_core(T, s_ov, stacks + (int64_t)b * cap, len, q_in, tok, cap, lane, ptr, ov, q);
+    const int res = advance_core<kPlain>(T, s_ov, stacks + (int64_t)b * cap, len, q_in, tok, cap, lane, ptr, ov, q);
     if (res == PSC_ADV_OK) {
         int32_t *dst = stacks + (int64_t)b * cap + ptr;
         for (int k = lane; k < ov; k += kWave) dst[k] = s_ov[k];
@@ -1518,6 +1574,7 @@ struct DecodeArgs {
 // token that is not advanced leaves the state as it was, and that state is
 // the one classified, exactly as psc_advance followed by
 // psc_compute_and_apply_dense.
+template <bool kPlain>
 __device__ __forceinline__ int decode_block_class(const int32_t *__restrict__ table, const DecodeArgs &D, int b,
                                                   uint32_t *__restrict__ err) {
     __shared__ int32_t s_cls;
@@ -1525,11 +1582,11 @@ __device__ __forceinline__ int decode_block_class(const int32_t *__restrict__ ta
     if (threadIdx.x < kWave) {
         const int lane = threadIdx.x;
         const int cap = D.cap;
-        const int tok = D.tokens[b];
-        const int len = D.lens_in[b], q_in = D.qs_in[b];
+        hold(D.T);
+        const int tok = uniform(D.tokens + b), len = uniform(D.lens_in + b), q_in = uniform(D.qs_in + b);
         const int32_t *st = D.stacks_in + (int64_t)b * cap;
         int ptr, ov, q;
-        const int res = advance_core(D.T, s_ov, st, len, q_in, tok, cap, lane, ptr, ov, q);
+        const int res = advance_core<kPlain>(D.T, s_ov, st, len, q_in, tok, cap, lane, ptr, ov, q);
         const int new_len = res == PSC_ADV_OK ? ptr + ov : len;
         if (blockIdx.x == 0) {
             int32_t *dst = D.stacks_out + (int64_t)b * cap;
@@ -1557,16 +1614,18 @@ __device__ __forceinline__ int decode_block_class(const int32_t *__restrict__ ta
 // psc_decode_step's first launch when its grid would not fit on the GPU at
 // once: one wavefront per sequence advances it and writes the new state
 // (the second launch is the fused step on the new states).
+template <bool kPlain>
 __global__ void __launch_bounds__(kWave)
 advance_copy_kernel(DecodeArgs D) {
     __shared__ int32_t s_ov[kOverlay];
     const int b = blockIdx.x;
     const int lane = threadIdx.x;
     const int cap = D.cap;
-    const int len = D.lens_in[b], q_in = D.qs_in[b];
+    hold(D.T);
+    const int tok = uniform(D.tokens + b), len = uniform(D.lens_in + b), q_in = uniform(D.qs_in + b);
     const int32_t *st = D.stacks_in + (int64_t)b * cap;
     int ptr, ov, q;
-    const int res = advance_core(D.T, s_ov, st, len, q_in, D.tokens[b], cap, lane, ptr, ov, q);
+    const int res = advance_core<kPlain>(D.T, s_ov, st, len, q_in, tok, cap, lane, ptr, ov, q);
     int32_t *dst = D.stacks_out + (int64_t)b * cap;
     const int keep = res == PSC_ADV_OK ? ptr : min(max(len, 0), cap);
     for (int k = lane; k < keep; k += kWave) dst[k] = st[k];
@@ -1578,24 +1637,24 @@ advance_copy_kernel(DecodeArgs D) {
     }
 }
 
-template <bool kBf16, bool kSliced>
+template <bool kBf16, bool kSliced, bool kPlain>
 __global__ void __launch_bounds__(kFusedBlock)
 decode_fast_kernel(const int32_t *__restrict__ table, const uint32_t *__restrict__ masks, int32_t mask_stride,
                    const int32_t *__restrict__ ids, DecodeArgs D, int32_t V, int32_t W, int32_t select_dense,
                    uint32_t *__restrict__ out, uint32_t *__restrict__ err, void *__restrict__ logits) {
     const int b = blockIdx.y;
     const Row<kBf16> R(logits, b, V);
-    const int cls = decode_block_class(table, D, b, err);
+    const int cls = decode_block_class<kPlain>(table, D, b, err);
     fused_fast_apply<kBf16, kSliced>(cls, b, R, masks, mask_stride, ids, W, select_dense, out);
 }
 
-template <bool kBf16, bool kSliced>
+template <bool kBf16, bool kSliced, bool kPlain>
 __global__ void __launch_bounds__(kBlock)
 decode_generic_kernel(const int32_t *__restrict__ table, const uint32_t *__restrict__ masks, int32_t mask_stride,
                       const int32_t *__restrict__ ids, DecodeArgs D, int32_t V, int32_t W,
                       uint32_t *__restrict__ out, uint32_t *__restrict__ err, void *__restrict__ logits) {
     const int b = blockIdx.y;
-    const int cls = decode_block_class(table, D, b, err);
+    const int cls = decode_block_class<kPlain>(table, D, b, err);
     fused_generic_apply<kBf16, kSliced>(cls, b, masks, mask_stride, ids, V, W, out, logits);
 }
 
@@ -1949,10 +2008,12 @@ AdvTables adv_tables(const psc_handle *h) {
     const int32_t *g = reinterpret_cast<const int32_t *>(base + h->gram_off);
     const psc::AdvanceLayout &L = h->adv;
     const int32_t *action = h->action_packed ? reinterpret_cast<const int32_t *>(base + h->packed_off) : g + L.action;
-    return AdvTables{g + L.lex_next, g + L.lex_accept, g + L.ignored, action, g + L.go, g + L.prod_lhs,
-                     g + L.prod_len, g + L.tok_off, reinterpret_cast<const uint8_t *>(base + h->vbytes_off),
+    return AdvTables{g + L.lex_accept, g + L.ignored, action, g + L.go, g + L.prod_lhs, g + L.prod_len,
+                     reinterpret_cast<const int32_t *>(base + h->records_off),
+                     reinterpret_cast<const uint8_t *>(base + h->vbytes_off), base + h->steps_off,
                      h->n_lex, h->n_lr, L.n_term, L.n_nt, L.end_term, L.eos, h->V, h->action_packed ? 1 : 0,
-                     h->has_closure ? reinterpret_cast<const int32_t *>(base + h->closure_off) : nullptr};
+                     lexer_steps_wide(*h) ? 1 : 0,
+                     h->has_closure ? reinterpret_cast<const i32x2 *>(base + h->closure_off) : nullptr};
 }
 
 // Workgroups of 256 threads that fit on the current GPU at once: 8 per
@@ -1986,11 +2047,13 @@ extern "C" psc_status psc_bind_device_ex(psc_handle *h, void *dev_buf, size_t nb
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     char *base = static_cast<char *>(dev_buf);
     // the tables derived at bind time, on the host first
-    std::vector<int32_t> packed, closure, blocks;
+    std::vector<int32_t> packed, closure, blocks, records, steps;
     bool is_packed = false;
     try {
         is_packed = packed_action(*h, packed);
-        goto_closure(*h, closure);
+        goto_closure(*h, is_packed ? packed.data() : h->gram.data() + h->adv.action, closure);
+        token_records(*h, records);
+        lexer_steps(*h, steps);
         start_blocks(*h, blocks);
     } catch (const std::bad_alloc &) {
         set_error("psc_bind_device: out of host memory");
@@ -2012,6 +2075,8 @@ extern "C" psc_status psc_bind_device_ex(psc_handle *h, void *dev_buf, size_t nb
     put(L.gram, h->gram.data(), h->gram.size() * sizeof(int32_t));
     put(L.vbytes, h->vbytes.data(), h->vbytes.size());
     if (is_packed) put(L.packed, packed.data(), packed.size() * sizeof(int32_t));
+    put(L.records, records.data(), records.size() * sizeof(int32_t));
+    put(L.steps, steps.data(), steps.size() * sizeof(int32_t));
     if (!closure.empty()) put(L.closure, closure.data(), closure.size() * sizeof(int32_t));
     // the predictor starts empty (-1 in every entry)
     if (e == hipSuccess)
@@ -2034,6 +2099,8 @@ extern "C" psc_status psc_bind_device_ex(psc_handle *h, void *dev_buf, size_t nb
     h->action_packed = is_packed;
     h->closure_off = L.closure;
     h->has_closure = !closure.empty();
+    h->records_off = L.records;
+    h->steps_off = L.steps;
     h->pred_off = L.pred;
     h->info.bound_mask_layout = L.sliced ? PSC_BIND_SLICED : PSC_BIND_FLAT;
     return PSC_OK;
@@ -2239,9 +2306,13 @@ extern "C" psc_status psc_advance(const psc_handle *h, int32_t *stacks, int32_t 
     }
     if (B == 0) return PSC_OK;
     const AdvTables T = adv_tables(h);
-    hipLaunchKernelGGL(advance_kernel, dim3(B), dim3(kWave), 0,
-                       reinterpret_cast<hipStream_t>(stream), T, stacks, cap, stack_lens, lexer_states, B, tokens,
-                       status);
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    if (T.plain())
+        hipLaunchKernelGGL(advance_kernel<true>, dim3(B), dim3(kWave), 0, s, T, stacks, cap, stack_lens, lexer_states,
+                           B, tokens, status);
+    else
+        hipLaunchKernelGGL(advance_kernel<false>, dim3(B), dim3(kWave), 0, s, T, stacks, cap, stack_lens, lexer_states,
+                           B, tokens, status);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? PSC_OK : device_fail("psc_advance", e);
 }
@@ -2288,7 +2359,8 @@ extern "C" psc_status psc_decode_step(const psc_handle *h, const int32_t *stacks
     const int waves = kFusedBlock / kWave;
     const int64_t segments = fast ? (tiles_of(logits, bf16, V) + waves - 1) / waves : (W + kGenWords - 1) / kGenWords;
     if (segments * B > resident_blocks()) {
-        hipLaunchKernelGGL(advance_copy_kernel, dim3(B), dim3(kWave), 0, s, D);
+        if (D.T.plain()) hipLaunchKernelGGL(advance_copy_kernel<true>, dim3(B), dim3(kWave), 0, s, D);
+        else hipLaunchKernelGGL(advance_copy_kernel<false>, dim3(B), dim3(kWave), 0, s, D);
         hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return device_fail(what, e0);
         return launch_fused(h, stacks_out, cap, kUnbounded, lens_out, qs_out, B, out_bitmask, logits, dtype, V, stream,
@@ -2296,22 +2368,34 @@ extern "C" psc_status psc_decode_step(const psc_handle *h, const int32_t *stacks
     }
     const dim3 grid((unsigned)segments, B);
     if (fast) {
-#define PSC_DECODE_FAST(BF, SL)                                                                                      \
-    hipLaunchKernelGGL((decode_fast_kernel<BF, SL>), grid, dim3(kFusedBlock), 0, s, T.table, T.masks, T.mstride, T.ids, \
-                       D, V, W, 1, out_bitmask, T.err, logits)
-        if (bf16 && T.sliced) PSC_DECODE_FAST(true, true);
-        else if (bf16) PSC_DECODE_FAST(true, false);
-        else if (T.sliced) PSC_DECODE_FAST(false, true);
-        else PSC_DECODE_FAST(false, false);
+#define PSC_DECODE_FAST(BF, SL, PL)                                                                                    \
+    hipLaunchKernelGGL((decode_fast_kernel<BF, SL, PL>), grid, dim3(kFusedBlock), 0, s, T.table, T.masks, T.mstride,  \
+                       T.ids, D, V, W, 1, out_bitmask, T.err, logits)
+#define PSC_DECODE_FAST_T(PL)                                                                                          \
+    do {                                                                                                             \
+        if (bf16 && T.sliced) PSC_DECODE_FAST(true, true, PL);                                                         \
+        else if (bf16) PSC_DECODE_FAST(true, false, PL);                                                               \
+        else if (T.sliced) PSC_DECODE_FAST(false, true, PL);                                                           \
+        else PSC_DECODE_FAST(false, false, PL);                                                                        \
+    } while (0)
+        if (D.T.plain()) PSC_DECODE_FAST_T(true);
+        else PSC_DECODE_FAST_T(false);
+#undef PSC_DECODE_FAST_T
 #undef PSC_DECODE_FAST
     } else {
-#define PSC_DECODE_GEN(BF, SL)                                                                                       \
-    hipLaunchKernelGGL((decode_generic_kernel<BF, SL>), grid, dim3(kBlock), 0, s, T.table, T.masks, T.mstride, T.ids,   \
-                       D, V, W, out_bitmask, T.err, logits)
-        if (bf16 && T.sliced) PSC_DECODE_GEN(true, true);
-        else if (bf16) PSC_DECODE_GEN(true, false);
-        else if (T.sliced) PSC_DECODE_GEN(false, true);
-        else PSC_DECODE_GEN(false, false);
+#define PSC_DECODE_GEN(BF, SL, PL)                                                                                    \
+    hipLaunchKernelGGL((decode_generic_kernel<BF, SL, PL>), grid, dim3(kBlock), 0, s, T.table, T.masks, T.mstride,  \
+                       T.ids, D, V, W, out_bitmask, T.err, logits)
+#define PSC_DECODE_GEN_T(PL)                                                                                          \
+    do {                                                                                                             \
+        if (bf16 && T.sliced) PSC_DECODE_GEN(true, true, PL);                                                         \
+        else if (bf16) PSC_DECODE_GEN(true, false, PL);                                                               \
+        else if (T.sliced) PSC_DECODE_GEN(false, true, PL);                                                           \
+        else PSC_DECODE_GEN(false, false, PL);                                                                        \
+    } while (0)
+        if (D.T.plain()) PSC_DECODE_GEN_T(true);
+        else PSC_DECODE_GEN_T(false);
+#undef PSC_DECODE_GEN_T
 #undef PSC_DECODE_GEN
     }
     hipError_t e = hipGetLastError();

@@ -114,6 +114,8 @@ struct AdvanceLayout {
 //   [argmax_off, ...)          masked argmax: [65536] records of 128 bytes, each a uint64
 //                              slot then a uint32 arrival counter (zero between calls)
 //   [packed_off, ...)          int32 ACTION with packed reductions (packed_action)
+//   [records_off, ...)         int32 token records [V][kTokenInts] (token_records)
+//   [steps_off, ...)           int32 lexer steps (lexer_steps)
 //   [closure_off, ...)         int32 unit-reduction closure of GOTO (goto_closure), when it fits
 //   [pred_off, ...)            int32 class predictor [start_block_count(n_lex)][64][2]: for
 //                              lexer state q and the way a walk's first step from start[q]
@@ -124,6 +126,8 @@ constexpr int kCounterFaults = 0, kCounterPredUpdates = 1;
 constexpr int kSliceWords = 64;           // words per slice of a mask row (the sliced layout)
 constexpr int kPredInts = 64 * 2;         // predictor slots per lexer state
 constexpr int kStartBlockInts = 64 * 4;   // one 16-byte vector per lane
+constexpr int kTokenInts = 8;             // a token's record: offset, length, first kTokenBytes bytes
+constexpr int kTokenBytes = (kTokenInts - 2) * 4;
 // Lexer states q < kMaxStartBlocks have a start block (at most 4 MB); a walk
 // from a higher one reads start[q]'s row after start[q], as any other row.
 constexpr int32_t kMaxStartBlocks = 4096;
@@ -156,7 +160,7 @@ struct psc_handle {
     size_t dev_bytes = 0;
     int device = -1;               // the HIP device current at bind time
     size_t mask_off = 0, ids_off = 0, gram_off = 0, vbytes_off = 0, argmax_off = 0, packed_off = 0,
-           closure_off = 0, pred_off = 0;
+           closure_off = 0, pred_off = 0, records_off = 0, steps_off = 0;
     bool sliced = false;           // the bound mask table is the sliced layout
     uint32_t options = 0;          // PSC_OPT_* (psc_set_options)
     bool action_packed = false;    // the device ACTION copy carries each reduction's length and lhs
@@ -172,16 +176,29 @@ void set_error(const std::string &msg);
 // empty) when some production does not fit (length > 255 or lhs >= 2^21).
 bool packed_action(const psc_handle &h, std::vector<int32_t> &out);
 // GOTO followed by the unit reductions the lookahead then selects:
-// closure[(s * n_nt + A) * n_term + t] is the state on top after a reduction
-// to A returns to state s with lookahead t, GOTO[s][A] pushed and every
-// following reduction by a one-symbol production done (each pops the state
-// just pushed and pushes GOTO[s][B], so s stays below); -1 where a GOTO in
-// that run is missing.  A run longer than n_nt (a cycle of unit
-// productions) is left undone: the entry is GOTO[s][A].  Only built when it
-// takes at most kClosureMaxBytes.
-constexpr size_t kClosureMaxBytes = 64u << 20;
+// closure[(s * n_nt + A) * n_term + t] is (g, a): g is the state on top after a
+// reduction to A returns to state s with lookahead t, GOTO[s][A] pushed and
+// every following reduction by a one-symbol production done (each pops the
+// state just pushed and pushes GOTO[s][B], so s stays below), and a is
+// action[g][t] (`action`: as the device reads it), so that the parse goes on
+// without another read; g = -1 where a GOTO in that run is missing.  A run
+// longer than n_nt (a cycle of unit productions) is left undone: g is
+// GOTO[s][A].  Only built for at most kClosureMaxEntries entries.
+constexpr size_t kClosureMaxEntries = 16u << 20;
 size_t goto_closure_bytes(const psc_handle &h);
-void goto_closure(const psc_handle &h, std::vector<int32_t> &out);
+void goto_closure(const psc_handle &h, const int32_t *action, std::vector<int32_t> &out);
+// The vocabulary as the device advance reads it, kTokenInts per token: the
+// offset of its spelling in the vocabulary bytes, its length, and its first
+// kTokenBytes bytes (four per int, the first one lowest; zeros past its end).
+void token_records(const psc_handle &h, std::vector<int32_t> &out);
+// One byte c in lexer state q, with what follows a byte that the pending lexeme
+// cannot take looked up beforehand: (the state it leads to or -1, the terminal
+// it ends or -1; an ignored one counts as none), [n_lex][256]: packed as
+// (state + 1) | (terminal + 1) << 16, or int32 pairs where that does not hold
+// them (lexer_steps_wide).
+bool lexer_steps_wide(const psc_handle &h);
+size_t lexer_steps_bytes(const psc_handle &h);
+void lexer_steps(const psc_handle &h, std::vector<int32_t> &out);
 // The start blocks, [start_block_count(n_lex)][kStartBlockInts]: block q is what a walk's
 // first step from start[q] loads, one 16-byte vector per lane (a chain
 // entry's 64 entries, or a sparse row's header and entries, as they are);
@@ -196,7 +213,7 @@ void slice_masks(psc_handle &h);
 // `flags` selects (PSC_BIND_FLAT or PSC_BIND_SLICED; 0 = the default).
 struct DeviceLayout {
     bool sliced;
-    size_t table, masks, ids, gram, vbytes, argmax, packed, closure, pred, total;
+    size_t table, masks, ids, gram, vbytes, argmax, packed, records, steps, closure, pred, total;
 };
 DeviceLayout device_layout(const psc_handle &h, uint32_t flags);
 }

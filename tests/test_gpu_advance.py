@@ -274,3 +274,104 @@ def test_decode_step_rejects_overlapping_states(built):
                                          ds.stacks.data_ptr(), ds.lens.data_ptr(), ds.qs.data_ptr(), 16, 4,
                                          t.data_ptr(), ds.status.data_ptr(), None, logits.data_ptr(),
                                          psc.PSC_F32, wl.V, None))
+
+
+@pytest.mark.parametrize("words,run", [(3, 0), (150, 0), (3, 260)])
+def test_advance_token_lengths_and_deep_pops(words, run):
+    """Spellings of 1 to 70 bytes (around the 24 that a token's record holds and
+    its refills), single tokens that pop past the 64 staged symbols, and, with
+    `run`, a production too long for packed reductions; every step against the
+    host parse of all the bytes fed so far."""
+    kw = [b"k" + bytes([97 + i % 26, 97 + i // 26]) * 3 for i in range(words)]
+    text = "%start s\nN: /[0-9]+/\ns: e | s \";\" e\ne: N | \"(\" e \")\"" + "".join(' | "%s" e' % k.decode() for k in kw)
+    if run:
+        text += ' | "#" ' + '"~" ' * run
+    sizes = [1, 2, 7, 8, 9, 15, 16, 17, 23, 24, 25, 31, 32, 33, 63, 64, 65, 70]
+    toks = [c * n for n in sizes for c in (b"(", b")", b"7")] + [k + t for k in kw for t in (b"", b"(")]
+    toks += [k[:4] for k in kw[:3]] + [b";", b"1" * 20 + b")" * 9, b")" * 30 + b";" + kw[-1] * 3 + b"5", b"x", b"9x", b"();"]
+    toks += [b"#" + b"~" * 50, b"~" * 60, b"~" * 10, b"~~;", b"~"] * (3 if run else 0)
+
+    class Vocab:
+        tokens = toks + [b""]
+        eos_id = len(toks)
+    clf = psc.Classifier.from_text(text + "\n", Vocab).bind(DEV)
+    rng = np.random.default_rng(words)
+    B, cap = 64, run + 100
+    ds = DecodeStates(clf, B, cap, DEV)
+    text = [b"#" + b"~" * run + b";" if run and b % 4 == 1 else b"" for b in range(B)]
+    want = [clf.host_state(t) for t in text]
+    ds.load(want)
+    seen = set()
+
+    def viable(t):
+        try:
+            return bool(clf.host_state(t))
+        except psc.PscError:
+            return False
+
+    def step(b, t):
+        """(status, state) after token t of sequence b."""
+        try:
+            st = clf.host_state(text[b] + toks[t])
+        except psc.PscError:
+            return psc.ADV_REJECTED, want[b]
+        return (psc.ADV_OK, st) if len(st[1]) <= cap else (psc.ADV_OVERFLOW, want[b])
+
+    for k in range(60):
+        picked, expect = [], []
+        for b in range(B):
+            for _ in range(1 if b % 8 == k % 8 else 30):     # mostly valid tokens, sometimes any
+                t = int(rng.integers(0, len(toks)))
+                got = step(b, t)
+                if got[0] == psc.ADV_OK and any(viable(text[b] + toks[t] + c) for c in (b";", b"(", b")", b"7")):
+                    break
+            if b == (k * 7) % B:
+                t, got = -1, (psc.ADV_SKIPPED, want[b])
+            elif got[0] == psc.ADV_OK:
+                text[b] += toks[t]
+            picked.append(t)
+            expect.append(got)
+        st = ds.advance(torch.tensor(picked, dtype=torch.int32, device=DEV)).cpu().numpy()
+        want = [e[1] for e in expect]
+        seen |= {e[0] for e in expect}
+        assert [int(s) for s in st] == [e[0] for e in expect], k
+        assert _same_states(ds.host_states(), want) < 0, k
+    assert seen >= {psc.ADV_OK, psc.ADV_REJECTED, psc.ADV_SKIPPED}
+    assert run or psc.ADV_OVERFLOW in seen
+    assert not run or any(t.startswith(b"#" + b"~" * run + b";") and len(t) > run + 2 for t in text)   # the long reduction
+
+
+def test_advance_many_lexer_states():
+    """A lexer of 66,000 states, too many for packed lexer steps (16 bits of
+    state), against the host parse."""
+    n = 66000
+    nxt = np.full((n, 256), -1, np.int32)
+    nxt[np.arange(n - 1), ord("a")] = np.arange(1, n)
+    nxt[n - 1, ord("a")] = n - 1
+    nxt[0, ord("b")] = 1
+    accept = np.full(n, -1, np.int32)
+    accept[1:] = 0
+
+    class Lexer:
+        next = nxt
+
+    class Grammar:        # s -> A | s A
+        lexer, terminal_ignored, end_terminal = Lexer, np.zeros(2, np.uint8), 1
+        action = np.array([[5, 0], [2, 2], [13, 3], [6, 6]], np.int32)
+        goto = np.array([[2], [-1], [-1], [-1]], np.int32)
+        prod_lhs, prod_len = np.array([0, 0], np.int32), np.array([1, 2], np.int32)
+    Lexer.accept = accept
+
+    class Vocab:
+        tokens = [b"a", b"a" * 30, b"ab", b"bbb" + b"a" * 50, b"c", b""]
+        eos_id = 5
+    clf = psc.Classifier(Grammar, Vocab).bind(DEV)
+    text = [b"", b"a" * 10, b"a" * 65510, b"a" * 65535, b"a" * 65998, b"a" * 65999 + b"ba"]
+    ds = DecodeStates(clf, len(text), 64, DEV).load([clf.host_state(t) for t in text])
+    for k in range(10):
+        toks = [(k + b) % 5 for b in range(len(text))]
+        st = ds.advance(torch.tensor(toks, dtype=torch.int32, device=DEV)).cpu().numpy()
+        for b, t in enumerate(toks):
+            assert st[b] == (psc.ADV_REJECTED if t == 4 else psc.ADV_OK)
+            text[b] += Vocab.tokens[t] if t != 4 else b""
+        assert _same_states(ds.host_states(), [clf.host_state(t) for t in text]) < 0, k
