@@ -357,8 +357,6 @@ struct WalkRun {
 // The lengths of sequences i0 + k * kWave + lane, k < kN, loaded in one
 // round trip (every load issued before the first is used), negative ones as
 // zero, summed per lane.
-constexpr int kLensPerRound = 4;
-
 template <int kN>
 __device__ __forceinline__ int64_t lens_round(__amdgpu_buffer_rsrc_t rl, int i0, int lane) {
     int v[kN];
@@ -371,9 +369,24 @@ __device__ __forceinline__ int64_t lens_round(__amdgpu_buffer_rsrc_t rl, int i0,
     return sum;
 }
 
+// The lane's part of the sum of lens[0 .. b): a buffer resource over them turns
+// the loads past b into zeros without a branch.  One round trip up to 1,024
+// sequences, with as few loads as b needs (rounds of four for all: 1,024 x
+// 32,000 bf16 13.3 us instead of 12.5, 700 x 4,001 5.55 instead of 5.45; rounds
+// of 16 past 256: 512 x 32,000 10.4 instead of 10.3).
+__device__ __forceinline__ int64_t lens_before(const int32_t *__restrict__ lens, int b, int lane) {
+    const __amdgpu_buffer_rsrc_t rl = wave_rsrc(lens, (uint32_t)b * 4u);
+    if (b <= kWave) return lens_round<1>(rl, 0, lane);
+    if (b <= 4 * kWave) return lens_round<4>(rl, 0, lane);
+    if (b <= 8 * kWave) return lens_round<8>(rl, 0, lane);
+    int64_t part = 0;
+    for (int i0 = 0; i0 < b; i0 += 16 * kWave) part += lens_round<16>(rl, i0, lane);
+    return part;
+}
+
 // One wavefront walks sequence b and returns its class, or -1 for an input
 // out of range.  Round trip 1 fetches lens[b], qs[b] and, for ragged stacks
-// (stride 0), the lengths before b (more round trips past 64 sequences):
+// (stride 0), the lengths before b (more round trips past 1,024 sequences):
 // the stack's offset, summed in 64 bits
 // (the stacks may hold more than 2^31 symbols in all), a negative length
 // counting as zero; a ragged stack reaching past n_stack symbols is an input
@@ -384,17 +397,7 @@ __device__ __forceinline__ int wave_class(const int32_t *__restrict__ table, int
                                           const int32_t *__restrict__ lens, const int32_t *__restrict__ qs,
                                           int b, int lane) {
     const int own = *((lane & 1) ? qs + b : lens + b);
-    int64_t part = 0;
-    if (stride == 0) {
-        // a buffer resource over lens[0..b) turns the loads past b into
-        // zeros without a branch
-        const __amdgpu_buffer_rsrc_t rl = wave_rsrc(lens, (uint32_t)b * 4u);
-        if (b <= kWave) {
-            part = lens_round<1>(rl, 0, lane);
-        } else {
-            for (int i0 = 0; i0 < b; i0 += kLensPerRound * kWave) part += lens_round<kLensPerRound>(rl, i0, lane);
-        }
-    }
+    const int64_t part = stride == 0 ? lens_before(lens, b, lane) : 0;
     const int len = __builtin_amdgcn_readlane(own, 0);
     const int q = __builtin_amdgcn_readlane(own, 1);
     const int64_t off = stride ? (int64_t)b * stride : wave_sum(part);
@@ -432,15 +435,7 @@ __device__ __forceinline__ void wave_begin(const int32_t *__restrict__ table, in
                                            const int32_t *__restrict__ qs, const int32_t *__restrict__ pred, int b,
                                            int lane, WalkRun &r) {
     const int own = *((lane & 1) ? qs + b : lens + b);
-    int64_t part = 0;
-    if (stride == 0) {
-        const __amdgpu_buffer_rsrc_t rl = wave_rsrc(lens, (uint32_t)b * 4u);
-        if (b <= kWave) {
-            part = lens_round<1>(rl, 0, lane);
-        } else {
-            for (int i0 = 0; i0 < b; i0 += kLensPerRound * kWave) part += lens_round<kLensPerRound>(rl, i0, lane);
-        }
-    }
+    const int64_t part = stride == 0 ? lens_before(lens, b, lane) : 0;
     const int len = __builtin_amdgcn_readlane(own, 0);
     const int q = __builtin_amdgcn_readlane(own, 1);
     const int64_t off = stride ? (int64_t)b * stride : wave_sum(part);

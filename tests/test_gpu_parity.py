@@ -187,3 +187,20 @@ def test_classes_reject_out_of_range(built):
     want = clf.classify_host([good])[0]
     assert got.tolist() == [want, -1, -1, want]
     assert clf.error_count(reset=True) == 2
+
+
+@pytest.mark.parametrize("B", [64, 65, 256, 257, 512, 513, 1024, 1025, 2100])
+def test_ragged_offsets_at_every_batch_size(built, B):
+    """A ragged stack starts at the sum of the lengths before it, taken in
+    rounds of 64 to 1,024: the last sequences of a round and the first of the
+    next, against the host walk."""
+    wl, clf, _orc = built("json")
+    pool = wl.states(3) + wl.states(41)
+    rng = np.random.default_rng(B)
+    states = [pool[i] for i in rng.integers(0, len(pool), B)]
+    packed = pack_states(states, DEV)
+    want = clf.classify_host(states)
+    assert np.array_equal(clf.compute_classes(*packed).cpu().numpy(), want)
+    got = clf.compute_masks(*packed).cpu().numpy().view(np.uint32)
+    rows = {int(c): clf.class_mask(int(c)) for c in set(want.tolist())}
+    assert all(np.array_equal(got[b], rows[int(want[b])]) for b in range(B))
