@@ -2016,6 +2016,52 @@ AdvTables adv_tables(const psc_handle *h) {
 // it), from the device's compute-unit count.
 int64_t resident_blocks() { return (int64_t)compute_units() * 8; }
 
+// Rows of V logits that one launch of the apply takes: their elements are
+// counted in 31 bits where the rows are masked as one long row (whole mask
+// words), and a launch holds less than 2^32 threads, which 69 GB of bf16 rows
+// of 513 would pass (one wavefront per tile).
+int64_t apply_rows(const void *logits, bool bf16, int32_t V) {
+    if (V % 32 == 0) return INT32_MAX / V;
+    if (V < kShortRow || !vector_path(logits, bf16)) return INT32_MAX;
+    constexpr int64_t kMostBlocks = ((int64_t)1 << 32) / kBlock - 1;
+    return kMostBlocks * (kBlock / kWave) / tiles_of(logits, bf16, V);
+}
+
+// One launch of psc_apply_mask, on at most apply_rows rows.
+void launch_apply(void *logits, bool bf16, const uint32_t *bitmask, int32_t B, int32_t V, int32_t select_dense,
+                  hipStream_t s) {
+    // rows of whole words are one long row: the bits are contiguous as well
+    if (V % 32 == 0) {
+        V *= B;
+        B = 1;
+    }
+    const int32_t W = (int32_t)(((int64_t)V + 31) / 32);
+    if (V >= kShortRow && vector_path(logits, bf16)) {
+        const uint32_t tiles = (uint32_t)tiles_of(logits, bf16, V);
+        const uint64_t waves = (uint64_t)tiles * B;
+        const unsigned blocks = (unsigned)((waves + kBlock / kWave - 1) / (kBlock / kWave));
+        if (bf16)
+            hipLaunchKernelGGL(apply_fast_kernel<true>, dim3(blocks), dim3(kBlock), 0, s, logits, bitmask, V, W, tiles,
+                               waves, select_dense);
+        else
+            hipLaunchKernelGGL(apply_fast_kernel<false>, dim3(blocks), dim3(kBlock), 0, s, logits, bitmask, V, W,
+                               tiles, waves, select_dense);
+        return;
+    }
+    const int64_t n = (int64_t)B * V;
+    const int64_t blocks = std::min<int64_t>((n + kBlock - 1) / kBlock, 65536);
+#define PSC_APPLY(BF, IX)                                                                                            \
+    hipLaunchKernelGGL((apply_generic_kernel<BF, IX>), dim3((unsigned)blocks), dim3(kBlock), 0, s, logits, bitmask,   \
+                       (IX)n, V, W)
+    // 32-bit division where the element index and the stride past it fit
+    const bool narrow = n < ((int64_t)1 << 31);
+    if (bf16 && narrow) PSC_APPLY(true, uint32_t);
+    else if (bf16) PSC_APPLY(true, int64_t);
+    else if (narrow) PSC_APPLY(false, uint32_t);
+    else PSC_APPLY(false, int64_t);
+#undef PSC_APPLY
+}
+
 bool ranges_overlap(const void *a, const void *b, size_t n) {
     const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
     return x < y + n && y < x + n;
@@ -2410,43 +2456,16 @@ extern "C" psc_status psc_apply_mask(void *logits, psc_dtype dtype, const uint32
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const bool bf16 = dtype == PSC_BF16;
-    // rows of whole words are one long row: the bits are contiguous as well
-    if (V % 32 == 0 && (int64_t)B * V <= INT32_MAX) {
-        V *= B;
-        B = 1;
+    const bool select_dense = large_batch(bf16, B, V);
+    const int64_t W = ((int64_t)V + 31) / 32;
+    const int64_t rows = apply_rows(logits, bf16, V);
+    for (int64_t b = 0; b < B; b += rows) {
+        launch_apply(static_cast<char *>(logits) + b * V * (bf16 ? 2 : 4), bf16, bitmask + b * W,
+                     (int32_t)std::min<int64_t>(rows, B - b), V, select_dense, s);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return device_fail("psc_apply_mask", e);
     }
-    const int32_t W = (V + 31) / 32;
-    if (V >= kShortRow && vector_path(logits, bf16)) {
-        const uint32_t tiles = (uint32_t)tiles_of(logits, bf16, V);
-        const uint64_t waves = (uint64_t)tiles * B;
-        const uint64_t blocks = (waves + kBlock / kWave - 1) / (kBlock / kWave);
-        if (blocks > 0x7FFFFFFF) {
-            set_error("psc_apply_mask: tensor too large");
-            return PSC_E_INVALID_ARG;
-        }
-        const int32_t select_dense = large_batch(bf16, B, V);
-        if (bf16)
-            hipLaunchKernelGGL(apply_fast_kernel<true>, dim3((unsigned)blocks), dim3(kBlock), 0, s, logits, bitmask, V,
-                               W, tiles, waves, select_dense);
-        else
-            hipLaunchKernelGGL(apply_fast_kernel<false>, dim3((unsigned)blocks), dim3(kBlock), 0, s, logits, bitmask,
-                               V, W, tiles, waves, select_dense);
-    } else {
-        const int64_t n = (int64_t)B * V;
-        const int64_t blocks = std::min<int64_t>((n + kBlock - 1) / kBlock, 65536);
-#define PSC_APPLY(BF, IX)                                                                                            \
-    hipLaunchKernelGGL((apply_generic_kernel<BF, IX>), dim3((unsigned)blocks), dim3(kBlock), 0, s, logits, bitmask,   \
-                       (IX)n, V, W)
-        // 32-bit division where the element index and the stride past it fit
-        const bool narrow = n < ((int64_t)1 << 31);
-        if (bf16 && narrow) PSC_APPLY(true, uint32_t);
-        else if (bf16) PSC_APPLY(true, int64_t);
-        else if (narrow) PSC_APPLY(false, uint32_t);
-        else PSC_APPLY(false, int64_t);
-#undef PSC_APPLY
-    }
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? PSC_OK : device_fail("psc_apply_mask", e);
+    return PSC_OK;
 }
 
 extern "C" psc_status psc_device_error_count(const psc_handle *h, uint32_t *out, int32_t reset, void *stream) {

@@ -56,3 +56,24 @@ def test_large_batch_dense_and_sparse(dtype, B, V, offset):
     dense = torch.randint(-2**31, 2**31, (B // 2, W), device=DEV, dtype=torch.int64).to(torch.int32)
     bits[:B // 2] = dense
     _check(B, V, dtype, offset, bits)
+
+
+@pytest.mark.parametrize("V,B", [(513, 2**26 + 4101), (544, 2**22 + 5), (480, 2**23 + 3), (33, 2**26 + 77)])
+def test_apply_past_one_launch(V, B):
+    """More wavefronts than one launch can hold (rows of 513: 69 GB), and more
+    elements than 31 bits count, of rows of whole mask words and of short ones.
+    The masks have a period of 64 rows, so every 2^20 rows end the same."""
+    torch.cuda.empty_cache()
+    W, dtype, part = (V + 31) // 32, torch.bfloat16, 2**20
+    period = _mixed_bits(64, W, V)
+    bits = period.repeat((B + 63) // 64, 1)[:B]
+    logits = torch.zeros(B, V, dtype=torch.int16, device=DEV)
+    apply_mask(logits.view(dtype), bits)
+    shift = torch.arange(32, device=DEV, dtype=torch.int32)
+    allowed = ((period[:, :, None] >> shift) & 1).bool().flatten(1)[:, :V]
+    inf = torch.tensor(float("-inf"), dtype=dtype).view(torch.int16).item()
+    want = torch.zeros(64, V, dtype=torch.int16, device=DEV).masked_fill_(~allowed, inf).repeat(part // 64, 1)
+    for b in range(0, B, part):
+        assert torch.equal(logits[b:b + part], want[:min(part, B - b)]), (V, b)
+    del logits, bits, want
+    torch.cuda.empty_cache()
