@@ -374,7 +374,9 @@ psc_status psc_predictor_updates(const psc_handle *h, uint32_t *out, int32_t res
  * psc_compute_and_apply_n with a per-wavefront timeline for profiling: every
  * wavefront of the launch writes one record of four uint64 to `records`
  * (device memory, n_records >= psc_timeline_records(h, B, dtype)), in the
- * order (sequence, slice, wavefront).  Times are ticks of the GPU's constant
+ * order (sequence, slice, wavefront); where the logits rows do not start at
+ * 128-byte lines, a row may need one workgroup more, which writes none.  Times
+ * are ticks of the GPU's constant
  * 100 MHz clock:
  *   [0] its start;
  *   [1] (after the walk's first step, with PSC_OPT_SPECULATE; else = start)

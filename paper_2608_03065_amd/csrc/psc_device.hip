@@ -812,18 +812,27 @@ __device__ __forceinline__ void fused_fast_apply(int cls, int b, const Row<kBf16
                      out ? out + (size_t)b * W : nullptr);
 }
 
-// A timeline record per wavefront (psc_compute_and_apply_timeline): its
-// start, the prediction known (t_a), its class known (t_b) and its last
+// Workgroups of a row of W whole mask words whose wavefronts write timeline
+// records, wherever the row starts.
+template <bool kBf16>
+__host__ __device__ constexpr int32_t timeline_slices(int32_t W) {
+    constexpr int32_t per = kFusedBlock / kWave * Tile<kBf16>::kWords;
+    return (W + per - 1) / per;
+}
+
+// A timeline record per wavefront (psc_compute_and_apply_timeline) of a
+// sequence's first `slices` workgroups: its start, the prediction known (t_a), its class known (t_b) and its last
 // store issued, in ticks of the GPU's constant 100 MHz clock; then the
 // wavefront, its XCD, whether the prediction held and whether the class was
 // known at the first step; then the sequence and the slice.
-__device__ __forceinline__ void timeline_record(unsigned long long *__restrict__ tl, unsigned long long t0,
-                                                unsigned long long t_a, unsigned long long t_b, uint32_t held,
-                                                uint32_t early) {
+__device__ __forceinline__ void timeline_record(unsigned long long *__restrict__ tl, uint32_t slices,
+                                                unsigned long long t0, unsigned long long t_a,
+                                                unsigned long long t_b, uint32_t held, uint32_t early) {
+    if (blockIdx.x >= slices) return;
     const unsigned long long t_e = wall_clock64();
     const uint32_t wave = threadIdx.x / kWave;
     const uint32_t xcc = __builtin_amdgcn_s_getreg((20) | (0 << 6) | (3 << 11)) & 15u;   // XCC_ID[3:0]
-    const size_t rec = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (blockDim.x / kWave) + wave;
+    const size_t rec = ((size_t)blockIdx.y * slices + blockIdx.x) * (blockDim.x / kWave) + wave;
     unsigned long long *o = tl + rec * 4;
     o[0] = t0;
     o[1] = (t_a - t0) | ((t_b - t0) << 32);
@@ -846,7 +855,7 @@ fused_fast_kernel(const int32_t *__restrict__ table, const uint32_t *__restrict_
     const int cls = block_class(table, n_lex, n_lr, stacks, stride, n_stack, lens, qs, b, err);
     if (kTl) t_b = wall_clock64();
     fused_fast_apply<kBf16, kSliced>(cls, b, R, masks, mask_stride, ids, W, select_dense, out);
-    if (kTl && (threadIdx.x & (kWave - 1)) == 0) timeline_record(tl, t0, t0, t_b, 0u, 0u);
+    if (kTl && (threadIdx.x & (kWave - 1)) == 0) timeline_record(tl, timeline_slices<kBf16>(W), t0, t0, t_b, 0u, 0u);
 }
 
 // psc_compute_and_apply, general path (any V, any element alignment): one
@@ -1029,7 +1038,8 @@ fused_spec_kernel(const int32_t *__restrict__ table, const uint32_t *__restrict_
         if (cls < 0) atomicAdd(counters + kCounterFaults, 1u);
         pred_update(pred, counters, r, cls);
     }
-    if (kTl && lane == 0) timeline_record(tl, t0, t_a, t_b, (uint32_t)(!done && cls == pc), (uint32_t)done);
+    if (kTl && lane == 0)
+        timeline_record(tl, gridDim.x, t0, t_a, t_b, (uint32_t)(!done && cls == pc), (uint32_t)done);
 }
 
 // ---------------------------------------------------------------- masked argmax
@@ -1785,9 +1795,6 @@ int32_t tiles_of(const void *logits, bool bf16, int32_t V) {
     const bool lines = line_rows(logits, bf16, V);
     return bf16 ? row_tiles<true>(V, lines) : row_tiles<false>(V, lines);
 }
-// The same wherever the rows start: the timeline's records are counted
-// before the logits are known.
-int32_t most_tiles(bool bf16, int32_t V) { return bf16 ? row_tiles<true>(V, false) : row_tiles<false>(V, false); }
 // Whether a call's densely mixed tiles are read, selected and written
 // (mask_tile): batches above kLargeBytes of logits, whose partial lines do not
 // stay in the Infinity Cache.  Three buffers used in turn, dense masks of a
@@ -1870,9 +1877,8 @@ psc_status launch_fused(const psc_handle *h, const int32_t *stacks, int32_t stri
     if (vector_path(logits, bf16)) {
         const bool spec = fast && (h->options & PSC_OPT_SPECULATE) != 0;
         const int32_t per = kFusedBlock / kWave;
-        const int32_t tiles = tl ? most_tiles(bf16, V) : tiles_of(logits, bf16, V);
-        const unsigned segments = spec && !tl ? (W + fused_words_per_block(bf16) - 1) / fused_words_per_block(bf16)
-                                              : (tiles + per - 1) / per;
+        const unsigned segments = spec ? (W + fused_words_per_block(bf16) - 1) / fused_words_per_block(bf16)
+                                       : (tiles_of(logits, bf16, V) + per - 1) / per;
         const FastArgs F{dim3(segments, B), s, T, h->n_lex, h->n_lr, h->n_classes, stacks, stride, n_stack, stack_lens,
                          lexer_states, W, out_bitmask, logits, V, buffer_per_step || large_batch(bf16, B, V), tl};
         if (bf16) launch_fast_dtype<true>(spec, T.sliced, tl != nullptr, F);
@@ -2205,8 +2211,8 @@ extern "C" psc_status psc_compute_and_apply_n(const psc_handle *h, const int32_t
 
 extern "C" int64_t psc_timeline_records(const psc_handle *h, int32_t B, psc_dtype dtype) {
     if (!h || B < 0) return 0;
-    const int32_t per = kFusedBlock / kWave;
-    return (int64_t)((most_tiles(dtype == PSC_BF16, h->V) + per - 1) / per) * B * per;
+    const int32_t slices = dtype == PSC_BF16 ? timeline_slices<true>(h->W) : timeline_slices<false>(h->W);
+    return (int64_t)slices * B * (kFusedBlock / kWave);
 }
 
 extern "C" psc_status psc_compute_and_apply_timeline(const psc_handle *h, const int32_t *stacks, int64_t n_stack,

@@ -232,3 +232,34 @@ def test_timeline_records_and_results(built):
     small = torch.zeros((n - 1, 4), dtype=torch.int64, device=DEV)
     with pytest.raises(Exception):
         clf.compute_and_apply_timeline(stacks, lens, qs, lg, small)
+
+
+@pytest.mark.parametrize("dtype,offset", [(torch.bfloat16, 0), (torch.bfloat16, 8), (torch.float32, 0),
+                                          (torch.float32, 4)])
+def test_timeline_records_of_whole_slices(dtype, offset):
+    """Rows of 8,192 fill their slices of 256 (bf16) or 128 (fp32) mask words:
+    as many records as wavefronts that hold them, also where the rows start 16
+    bytes past a 128-byte line, take one workgroup more, and nothing is written
+    past the records."""
+    V, B = 8192, 3
+
+    class Vocab:
+        tokens = [b"%d" % i if i % 3 else b"x%d" % i for i in range(V - 1)] + [b""]
+        eos_id = V - 1
+    clf = Classifier.from_text('%start v\nN: /[0-9]+/\nS: /"[a-z0-9]*"/\nv: N | S\n', Vocab).bind(DEV)
+    states = [clf.host_state(t) for t in (b"", b'"', b'"a')]
+    packed = pack_states(states, DEV)
+    slices = 1 if dtype == torch.bfloat16 else 2
+    n = clf.timeline_records(B, dtype)
+    assert n == slices * B * 4
+    rec = torch.zeros((n + 8, 4), dtype=torch.int64, device=DEV)
+    x = torch.randn(B, V).to(dtype)
+    lg = torch.zeros(offset + B * V, dtype=dtype, device=DEV)[offset:].view(B, V)
+    lg.copy_(x)
+    clf.compute_and_apply_timeline(*packed, lg, rec[:n])
+    torch.cuda.synchronize()
+    assert torch.equal(_as_int(lg.cpu()), _as_int(_closed_form(x, clf.masks_host(states), V)))
+    r = rec.cpu().numpy().view(np.uint64)
+    assert (r[:n, 0] > 0).all() and not r[n:].any()
+    where = [(int(a & 0xFFFFFFFF), int(a >> 32), int(m >> 32) & 7) for a, m in zip(r[:n, 3], r[:n, 2])]
+    assert where == [(b, i, w) for b in range(B) for i in range(slices) for w in range(4)]
