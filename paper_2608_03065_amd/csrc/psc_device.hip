@@ -1274,7 +1274,7 @@ argmax_partial_kernel(const int32_t *__restrict__ table, const uint32_t *__restr
                 best = umax64(best, argmax_tiles<kBf16, kTiles>(A, l));
             }
         } else {
-            // logits that are not at their elements' own alignment
+            // short rows, and logits that are not at their elements' own alignment
             const int v_end = (int)min((int64_t)V, ((int64_t)blockIdx.x + 1) * kGenWords * 32);
             for (int v = blockIdx.x * kGenWords * 32 + threadIdx.x; v < v_end; v += kFusedBlock) {
                 if (!((*mask_at<kSliced>(masks, mask_stride, ids, cls, v >> 5) >> (v & 31)) & 1u)) continue;
@@ -1908,8 +1908,10 @@ int compute_units() {
 }
 
 // Tiles of a row that one wavefront of the argmax takes (two at a time where
-// more than one): one where that gives at most 4 workgroups per compute unit,
-// otherwise as many as it takes for all workgroups to be on the GPU at once, 5
+// more than one): one where that gives at most 4 workgroups per compute unit
+// or a row has no more tiles than a workgroup wavefronts (a second one would be
+// empty and cost registers: 4,000 x 2,049 bf16 23.8 us with one, 32.1 with two,
+// 28.9 with a key per element; 4,000 x 8,192 25.8, 32.4 and 28.8); otherwise as many as it takes for all workgroups to be on the GPU at once, 5
 // per compute unit (the pair's registers), since each begins with its
 // sequence's walk and ends with two atomics.  us, 1 / 2 / 4 / 8 tiles a
 // wavefront: 8 x 32,000 bf16 (32 workgroups of one tile) 7.1 / 8.0 / 10.4 / 15.3;
@@ -1920,11 +1922,18 @@ int32_t argmax_tiles_per_wave(int32_t tiles, int32_t B) {
     const int64_t cus = compute_units();
     const int32_t waves = kFusedBlock / kWave;
     auto blocks = [&](int32_t per) { return (int64_t)((tiles + (int64_t)waves * per - 1) / ((int64_t)waves * per)) * B; };
-    if (blocks(1) <= 4 * cus) return 1;
+    if (tiles <= waves || blocks(1) <= 4 * cus) return 1;
     int32_t per = 2;
     while (blocks(per) > 5 * cus && waves * per < tiles) per *= 2;
     return per;
 }
+
+// Rows up to this many logits are read an element per thread: few tiles leave
+// wavefronts idle, and the ends of rows off a vector cost a second reduction.
+// us, elements / tiles: 1 x 513 bf16 5.0 / 6.0, 512 x 513 7.5 / 8.3, 4,000 x 513
+// 17.1 / 20.2; 64 x 1,025 bf16 7.6 / 8.2, fp32 7.5 / 7.8; 64 x 1,281 7.6 / 7.9,
+// 4,000 x 1,281 23.7 / 22.1; 64 x 1,793 8.2 / 8.3, 4,000 x 1,793 28.2 / 22.6.
+constexpr int32_t kArgmaxShortRow = 1280;
 
 // The masked argmax for ragged (stride 0) or strided stacks.
 // `records` is the per-sequence slot array (kArgmaxRecordWords uint64 per
@@ -1941,7 +1950,7 @@ psc_status launch_argmax(const psc_handle *h, const int32_t *stacks, int32_t str
     char *base = static_cast<char *>(h->dev_base);
     const Bound T = bound(h);
     const bool bf16 = dtype == PSC_BF16;
-    const int fast = vector_path(logits, bf16);
+    const int fast = V > kArgmaxShortRow && vector_path(logits, bf16);
     const int32_t W = h->W;
     const int32_t waves = kFusedBlock / kWave;
     const int32_t tiles = tiles_of(logits, bf16, V);

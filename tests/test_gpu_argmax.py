@@ -210,3 +210,61 @@ def test_argmax_rows_at_every_alignment(V, dtype):
         got = clf.compute_and_argmax(*pack_states(states, DEV), dev).cpu().numpy()
         want = _closed_form(x, bits, V)
         assert np.array_equal(got, want), (offset, np.nonzero(got != want)[0][:5])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("V,B,offset", [(1280, 90, 1), (1281, 90, 1), (4001, 1500, 0), (20001, 400, 3),
+                                        (20001, 700, 1), (70001, 700, 0)])
+def test_argmax_several_tiles_per_wavefront(V, B, offset, dtype):
+    """Rows around the change from elements to tiles, rows of a few tiles in a
+    large batch, and rows whose wavefronts take 2 to 16 tiles, two at a time,
+    all at odd alignments: the largest allowed logits (ties, NaNs, signed
+    zeros, denormals, -inf) stand at the first and last allowed token and on
+    either side of tile boundaries, so in both tiles of a pair, in later turns
+    and in a row's element-wise ends.  Token ids: compared exactly."""
+    class Vocab:
+        tokens = [b"%d" % (10 + i) if i % 3 else b"x%d" % i for i in range(V - 1)] + [b""]
+        eos_id = V - 1
+    clf = psc.Classifier.from_text('%start v\nN: /[0-9]+/\nS: /"[a-z0-9]*"/\nv: N | S\n', Vocab).bind(DEV)
+    kinds = [clf.host_state(t) for t in (b"", b'"')]
+    rows = [np.unpackbits(clf.class_mask(int(c)).astype("<u4").view(np.uint8), bitorder="little")[:V].astype(bool)
+            for c in clf.classify_host(kinds)]
+    line, tile = (64, 2048) if dtype == torch.bfloat16 else (32, 1024)
+    rng = np.random.default_rng(V + B)
+    x = rng.standard_normal((B, V), dtype=np.float32)
+    for b in range(B):
+        ids = np.nonzero(rows[b % 2])[0]
+        x[b, ~rows[b % 2]] = 50 if b % 3 else np.nan
+        cut = np.arange(tile, V + tile, tile) - (offset + b * V) % line      # first token of a tile
+        edges = np.searchsorted(ids, cut)
+        near = ids[np.unique(np.clip(np.concatenate([edges - 1, edges, [0, len(ids) - 1]]), 0, len(ids) - 1))]
+        pick = rng.choice(near, min(3, len(near)), replace=False)
+        if b % 10 < 4:
+            x[b, pick] = 20
+        elif b % 10 == 4:
+            x[b, pick] = 20
+            x[b, pick[:1]] = np.nan
+        elif b % 10 == 5:
+            x[b, pick[:2]] = np.nan
+        elif b % 10 == 6:
+            x[b, ids] = -1
+            x[b, pick] = [0.0, -0.0, 0.0][:len(pick)]
+        elif b % 10 == 7:
+            x[b, ids] = -np.inf
+        elif b % 10 == 8:
+            x[b, ids] = -np.abs(x[b, ids]) - 1
+            x[b, pick] = 1e-40
+        else:
+            x[b, pick] = np.inf
+    x = torch.from_numpy(x).to(dtype)
+    f = x.float().numpy()
+    want = []
+    for b in range(B):
+        ids = np.nonzero(rows[b % 2])[0]
+        nan = np.nonzero(np.isnan(f[b, ids]))[0]
+        want.append(ids[nan[0]] if nan.size else ids[int(np.argmax(f[b, ids]))])
+    buf = torch.full((offset + B * V + 64,), 99.0, dtype=dtype, device=DEV)
+    dev = buf[offset:offset + B * V].view(B, V)
+    dev.copy_(x)
+    got = clf.compute_and_argmax(*pack_states([kinds[b % 2] for b in range(B)], DEV), dev).cpu().numpy()
+    assert np.array_equal(got, want), np.nonzero(got != want)[0][:5]
