@@ -858,9 +858,10 @@ fused_fast_kernel(const int32_t *__restrict__ table, const uint32_t *__restrict_
     if (kTl && (threadIdx.x & (kWave - 1)) == 0) timeline_record(tl, timeline_slices<kBf16>(W), t0, t0, t_b, 0u, 0u);
 }
 
-// psc_compute_and_apply, general path (any V, any element alignment): one
-// workgroup per (sequence b, kGenWords mask words); the words go through LDS
-// and each thread then masks single elements.
+// psc_compute_and_apply an element per thread (short rows; logits that are not
+// at their elements' own alignment): one workgroup per (sequence b, kGenWords
+// mask words); the words go through LDS and each thread then masks single
+// elements.
 constexpr int kGenWords = 128;
 static_assert(kGenWords <= kBlock, "one pass stages the slice's words");
 
@@ -1782,7 +1783,7 @@ psc_status launch_classes(const psc_handle *h, const int32_t *stacks, int32_t st
     return launched(what);
 }
 
-// Whether the vector path takes rows of V logits: their elements at their own
+// Whether the logits can be taken by tiles: their elements at their own
 // alignment (any address a bf16 or fp32 tensor can have).
 bool vector_path(const void *logits, bool bf16) {
     return (reinterpret_cast<uintptr_t>(logits) & (bf16 ? 1 : 3)) == 0;
@@ -1803,6 +1804,18 @@ int32_t tiles_of(const void *logits, bool bf16, int32_t V) {
 // 44.3.
 constexpr int64_t kLargeBytes = (int64_t)104 << 20;
 bool large_batch(bool bf16, int32_t B, int32_t V) { return (int64_t)B * V * (bf16 ? 2 : 4) > kLargeBytes; }
+
+// Whether the step masks rows of V logits an element per thread: below 6 KiB
+// they fill no more than one and a half of a workgroup's four tiles, and a
+// wavefront's pass over a tile is longer than 256 threads' over the row.  us,
+// elements / tiles: 1 x 513 bf16 3.6 / 3.9, 512 x 513 5.3 / 5.8, 4,000 x 513
+// 11.1 / 12.9; 64 x 2,049 6.0 / 6.3; 512 x 3,073 6.95 / 7.02; 64 x 3,585
+// 6.5 / 6.35; fp32 64 x 1,025 5.66 / 5.99, 512 x 1,537 6.40 / 6.52, 512 x 1,793
+// 6.51 / 6.65, 64 x 2,049 6.01 / 5.95.
+constexpr int64_t kStepShortRow = 6 << 10;   // bytes
+bool step_by_element(const void *logits, bool bf16, int32_t V) {
+    return (int64_t)V * (bf16 ? 2 : 4) < kStepShortRow || !vector_path(logits, bf16);
+}
 
 // Words of the mask row per fused workgroup on the fast path.
 int32_t fused_words_per_block(bool bf16) {
@@ -1874,8 +1887,8 @@ psc_status launch_fused(const psc_handle *h, const int32_t *stacks, int32_t stri
     if (B == 0) return PSC_OK;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const Bound T = bound(h);
-    if (vector_path(logits, bf16)) {
-        const bool spec = fast && (h->options & PSC_OPT_SPECULATE) != 0;
+    const bool spec = fast && (h->options & PSC_OPT_SPECULATE) != 0;
+    if (spec || tl || !step_by_element(logits, bf16, V)) {
         const int32_t per = kFusedBlock / kWave;
         const unsigned segments = spec ? (W + fused_words_per_block(bf16) - 1) / fused_words_per_block(bf16)
                                        : (tiles_of(logits, bf16, V) + per - 1) / per;

@@ -8,7 +8,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2608_03065_amd.psc import apply_mask  # noqa: E402
+from paper_2608_03065_amd.psc import Classifier, apply_mask, pack_states  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -77,3 +77,30 @@ def test_apply_past_one_launch(V, B):
         assert torch.equal(logits[b:b + part], want[:min(part, B - b)]), (V, b)
     del logits, bits, want
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, 33), (torch.bfloat16, 513), (torch.bfloat16, 3071),
+                                     (torch.bfloat16, 3072), (torch.bfloat16, 3073), (torch.float32, 513),
+                                     (torch.float32, 1535), (torch.float32, 1536), (torch.float32, 1537)])
+@pytest.mark.parametrize("layout", ["flat", "sliced"])
+def test_step_rows_around_the_element_limit(dtype, V, layout):
+    """Rows below 6 KiB are masked an element per thread, longer ones by tiles:
+    the same logits and bitmask as the host walk's masks, at odd offsets."""
+    class Vocab:
+        tokens = [b"%d" % (10 + i) if i % 3 else b"x%d" % i for i in range(V - 1)] + [b""]
+        eos_id = V - 1
+    clf = Classifier.from_text('%start v\nN: /[0-9]+/\nS: /"[a-z0-9]*"/\nv: N | S\n', Vocab).bind(DEV, layout=layout)
+    states = [clf.host_state(t) for t in (b"", b'"', b"12", b'"a"')] * 17
+    bits = torch.from_numpy(clf.masks_host(states).view("int32")).to(DEV)
+    ints = torch.int16 if dtype == torch.bfloat16 else torch.int32
+    shift = torch.arange(32, device=DEV, dtype=torch.int32)
+    allowed = ((bits[:, :, None] >> shift) & 1).bool().flatten(1)[:, :V]
+    inf = torch.tensor(float("-inf"), dtype=dtype).view(ints).item()
+    for offset in (0, 1, 16):
+        n = len(states) * V
+        buf = torch.randint(-2**15, 2**15, (offset + n + 80,), device=DEV, dtype=torch.int32).to(ints)
+        want = buf.clone()
+        want[offset:offset + n].view(-1, V).masked_fill_(~allowed, inf)
+        out = torch.empty_like(bits)
+        clf.compute_and_apply(*pack_states(states, DEV), buf.view(dtype)[offset:offset + n].view(-1, V), out=out)
+        assert torch.equal(buf, want) and torch.equal(out, bits), offset
