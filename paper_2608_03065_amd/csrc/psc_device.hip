@@ -774,10 +774,15 @@ apply_fast_kernel(void *__restrict__ logits, const uint32_t *__restrict__ bits, 
                      [&](int32_t w) { return row[w]; }, nullptr);
 }
 
-// Short rows, and logits that are not at their elements' own alignment: one
-// element per thread.  A wavefront per tile would be mostly idle on short
-// rows (65,535 rows of 33: 4.8 us here, 15 us there; of 513: 53 against 9.6).
+// Short rows, small batches, and logits that are not at their elements' own
+// alignment: one element per thread.  A wavefront per tile would be mostly idle
+// on short rows (65,535 rows of 33: 4.8 us here, 15 us there; of 513: 53 against
+// 9.6), and on a GPU that is mostly idle itself its pass over a tile is longer
+// than a thread's over an element (us, here / there: 8 x 8,193 bf16 2.9 / 3.5,
+// 1 x 262,145 3.1 / 3.4, 64 x 8,193 3.2 / 3.5, 512 x 2,049 3.6 / 3.5; fp32
+// 8 x 32,001 3.0 / 3.1, 64 x 8,193 3.3 / 3.1).
 constexpr int32_t kShortRow = 512;
+constexpr int64_t kSmallBytes = (int64_t)3 << 19;
 
 template <bool kBf16, class Index>
 __global__ void __launch_bounds__(kBlock)
@@ -2064,7 +2069,7 @@ void launch_apply(void *logits, bool bf16, const uint32_t *bitmask, int32_t B, i
         B = 1;
     }
     const int32_t W = (int32_t)(((int64_t)V + 31) / 32);
-    if (V >= kShortRow && vector_path(logits, bf16)) {
+    if (V >= kShortRow && (int64_t)B * V * (bf16 ? 2 : 4) >= kSmallBytes && vector_path(logits, bf16)) {
         const uint32_t tiles = (uint32_t)tiles_of(logits, bf16, V);
         const uint64_t waves = (uint64_t)tiles * B;
         const unsigned blocks = (unsigned)((waves + kBlock / kWave - 1) / (kBlock / kWave));

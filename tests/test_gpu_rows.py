@@ -30,9 +30,10 @@ def _check(B, V, dtype, offset, bits):
     rows = want[offset:offset + B * V].view(B, V)
     inf = torch.tensor(float("-inf"), dtype=dtype).view(ints).item()
     shift = torch.arange(32, device=DEV, dtype=torch.int32)
-    for b0 in range(0, B, 8):       # in parts: the expanded bits are 4 bytes each
-        allowed = ((bits[b0:b0 + 8, :, None] >> shift) & 1).bool().flatten(1)[:, :V]
-        rows[b0:b0 + 8].masked_fill_(~allowed, inf)
+    part = max(8, 2**24 // V)
+    for b0 in range(0, B, part):       # in parts: the expanded bits are 4 bytes each
+        allowed = ((bits[b0:b0 + part, :, None] >> shift) & 1).bool().flatten(1)[:, :V]
+        rows[b0:b0 + part].masked_fill_(~allowed, inf)
     apply_mask(buf.view(dtype)[offset:offset + B * V].view(B, V), bits)
     torch.cuda.synchronize()
     assert torch.equal(buf, want), (B, V, dtype, offset)   # also what lies before and after the rows
@@ -41,9 +42,22 @@ def _check(B, V, dtype, offset, bits):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("V", [31, 511, 512, 513, 1023, 1025, 2047, 2048, 2049, 2111, 4096, 4160, 6145])
 def test_rows_at_every_alignment(V, dtype):
-    line = 64 if dtype == torch.bfloat16 else 32
+    line, item = (64, 2) if dtype == torch.bfloat16 else (32, 4)
+    many = (3 << 19) // (V * item) + line     # rows past the size below which elements are masked one by one
     for offset in (0, 1, 7, line // 2, line - 1):
-        _check(line + 3, V, dtype, offset, _mixed_bits(line + 3, (V + 31) // 32, V + offset))
+        for B in (line + 3, many):
+            _check(B, V, dtype, offset, _mixed_bits(B, (V + 31) // 32, V + offset))
+
+
+@pytest.mark.parametrize("dtype,B,V", [(torch.bfloat16, 3, 262143), (torch.bfloat16, 3, 262145),
+                                       (torch.bfloat16, 768, 1024), (torch.bfloat16, 767, 1024),
+                                       (torch.float32, 3, 131071), (torch.float32, 3, 131073),
+                                       (torch.float32, 1, 393216), (torch.float32, 1, 393184)])
+def test_apply_around_the_small_batch_limit(dtype, B, V):
+    """Batches below 1.5 MiB are masked an element per thread, larger ones by
+    tiles."""
+    for offset in (0, 1):
+        _check(B, V, dtype, offset, _mixed_bits(B, (V + 31) // 32, V))
 
 
 @pytest.mark.parametrize("dtype,B,V,offset", [(torch.bfloat16, 28, 2000001, 5), (torch.bfloat16, 27, 2097152, 0),
