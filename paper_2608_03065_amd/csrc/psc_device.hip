@@ -2095,6 +2095,20 @@ void launch_apply(void *logits, bool bf16, const uint32_t *bitmask, int32_t B, i
 #undef PSC_APPLY
 }
 
+// Whether the single-launch decoding step masks an element per thread: short
+// rows, as the step does, and grids of few workgroups, where a wavefront's pass
+// over a tile, whose code the advance before it has pushed out of the
+// instruction cache, is the longer way; in fp32, half the elements a tile, only
+// up to 4,096 logits a row.  us with real tokens, elements / tiles: 64 x 2,049
+// bf16 6.2 / 7.7, 8 x 65,537 7.7 / 8.5, 64 x 65,537 (1,088 workgroups) 9.3 / 9.9,
+// 512 x 8,193 (1,536) 9.0 / 9.3, 128 x 65,536 (2,048) 13.7 / 10.4; fp32 64 x 3,073
+// 6.6 / 7.0, 64 x 4,097 6.95 / 7.0, 64 x 8,192 7.3 / 7.2.
+constexpr int32_t kDecodeShortRow = 4096;   // fp32 logits
+bool decode_by_element(const void *logits, bool bf16, int32_t B, int32_t V) {
+    const int64_t blocks = ((int64_t)V + kGenWords * 32 - 1) / (kGenWords * 32) * B;
+    return step_by_element(logits, bf16, V) || (blocks <= 6 * (int64_t)compute_units() && (bf16 || V < kDecodeShortRow));
+}
+
 bool ranges_overlap(const void *a, const void *b, size_t n) {
     const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
     return x < y + n && y < x + n;
@@ -2425,7 +2439,7 @@ extern "C" psc_status psc_decode_step(const psc_handle *h, const int32_t *stacks
     const DecodeArgs D{adv_tables(h), stacks_in, lens_in, qs_in, stacks_out, lens_out, qs_out, tokens, status, cap};
     const int32_t W = h->W;
     const bool bf16 = dtype == PSC_BF16;
-    const bool fast = vector_path(logits, bf16);
+    const bool fast = !decode_by_element(logits, bf16, B, V);
     // When the fused grid does not fit on the GPU at once, workgroups that
     // start late would repeat the advance after the early ones finished:
     // then the advance runs once per sequence in a launch of its own and the

@@ -375,3 +375,64 @@ def test_advance_many_lexer_states():
             assert st[b] == (psc.ADV_REJECTED if t == 4 else psc.ADV_OK)
             text[b] += Vocab.tokens[t] if t != 4 else b""
         assert _same_states(ds.host_states(), [clf.host_state(t) for t in text]) < 0, k
+
+
+@pytest.mark.parametrize("layout", ["flat", "sliced"])
+@pytest.mark.parametrize("dtype,V,B", [
+    (torch.bfloat16, 513, 20), (torch.bfloat16, 3072, 1537), (torch.bfloat16, 3072, 1536), (torch.bfloat16, 4097, 768),
+    (torch.bfloat16, 4097, 769), (torch.bfloat16, 20001, 308), (torch.float32, 1536, 1537), (torch.float32, 4095, 40),
+    (torch.float32, 4096, 40), (torch.float32, 4097, 40), (torch.float32, 4097, 1100)])
+def test_decode_step_by_elements_and_by_tiles(dtype, V, B, layout):
+    """Rows and batches around the lines between an element per thread, tiles
+    and two launches (256 compute units), logits at an odd offset: states,
+    status, bitmask and logits against the host parse and walk."""
+    digits = [b"%d" % (10 + i) if i % 3 else b"x%d" % i for i in range(V - 5)]
+
+    class Vocab:
+        tokens = digits + [b'"', b"[", b"]", b",", b""]
+        eos_id = V - 1
+    clf = psc.Classifier.from_text('%start v\nN: /[0-9]+/\nS: /"[a-z0-9]*"/\nv: N | S | "[" l "]"\nl: v | l "," v\n',
+                                   Vocab).bind(DEV, layout=layout)
+    names = [b"[", b'"', digits[0], digits[1], b",", b"]"]
+    ids = {t: Vocab.tokens.index(t) for t in names}
+    ds = DecodeStates(clf, B, 64, DEV)
+    text = [b""] * B
+    # per residue of b: tokens that all parse, but for the last one of some
+    plans = [[b"[", digits[0], b",", b'"'], [b'"', digits[1], digits[0], b'"'], [b"[", b"[", digits[0], b"]"],
+             [digits[0], b"]", b",", b'"']]
+    ints = torch.int16 if dtype == torch.bfloat16 else torch.int32
+    inf = torch.tensor(float("-inf"), dtype=dtype).view(ints).item()
+    shift = torch.arange(32, device=DEV, dtype=torch.int32)
+    out = torch.empty((B, clf.W), dtype=torch.int32, device=DEV)
+    cache = {}
+
+    def viable(t):
+        if t not in cache:
+            try:
+                st = clf.host_state(t)
+                cache[t] = (st, torch.from_numpy(clf.masks_host([st])[0].view(np.int32)))
+            except psc.PscError:
+                cache[t] = None
+        return cache[t]
+
+    for k in range(4):
+        expect, toks = [], []
+        for b in range(B):
+            t = plans[b % 4][k]
+            skip = (b + k) % 11 == 5
+            ok = not skip and viable(text[b] + t) is not None
+            text[b] += t if ok else b""
+            toks.append(-1 if skip else ids[t])
+            expect.append(psc.ADV_SKIPPED if skip else psc.ADV_OK if ok else psc.ADV_REJECTED)
+        buf = torch.randint(-2**15, 2**15, (B * V + 81,), device=DEV, dtype=torch.int32).to(ints)
+        want = buf.clone()
+        st = ds.decode_step(torch.tensor(toks, dtype=torch.int32, device=DEV), buf.view(dtype)[1:1 + B * V].view(B, V),
+                            out=out)
+        assert st.tolist() == expect, k
+        assert _same_states(ds.host_states(), [viable(t)[0] for t in text]) < 0, k
+        bits = torch.stack([viable(t)[1] for t in text]).to(DEV)
+        rows = want[1:1 + B * V].view(B, V)
+        for b0 in range(0, B, 256):
+            allowed = ((bits[b0:b0 + 256, :, None] >> shift) & 1).bool().flatten(1)[:, :V]
+            rows[b0:b0 + 256].masked_fill_(~allowed, inf)
+        assert torch.equal(out, bits) and torch.equal(buf, want), k
