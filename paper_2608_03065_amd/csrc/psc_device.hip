@@ -592,8 +592,8 @@ __device__ __forceinline__ void store_inf(__amdgpu_buffer_rsrc_t rsrc, uint32_t 
 // there.  Only a batch whose partial lines do not fit it pays for them again,
 // as reads and writes of HBM: then (`select_dense`) a tile in which most words
 // are densely mixed is read, selected and written in 16-byte vectors instead
-// (256 x 262,144 bf16 of a programming language: 44 us against 62; of
-// generic JSON, sparsely masked: 39 against 32, and the stores stay).
+// (256 x 262,144 bf16 of a programming language, three buffers in turn: 38 us
+// against 57).
 template <bool kBf16>
 struct Tile {
     static constexpr int kElem = kBf16 ? 2 : 4;             // bytes per element
@@ -658,7 +658,7 @@ __device__ __forceinline__ bool any_of_quad(bool p) {
 // the end instead of a branch: the hardware drops such an access without a
 // memory request.  A 64-byte quad of vectors is written whole or not at all
 // (its kept vectors are read too): with the kept vectors left out, partial
-// lines reached HBM, 50.0 us instead of 44.1 at 256 x 262,144.
+// lines reached HBM, and 256 x 262,144 took 13% longer.
 template <bool kBf16>
 __device__ __forceinline__ void select_tile(__amdgpu_buffer_rsrc_t rsrc, uint32_t m, int lane) {
     using T = Tile<kBf16>;
@@ -1802,13 +1802,34 @@ int32_t tiles_of(const void *logits, bool bf16, int32_t V) {
     return bf16 ? row_tiles<true>(V, lines) : row_tiles<false>(V, lines);
 }
 // Whether a call's densely mixed tiles are read, selected and written
-// (mask_tile): batches above kLargeBytes of logits, whose partial lines do not
-// stay in the Infinity Cache.  Three buffers used in turn, dense masks of a
-// programming language, stores alone against this: 109 MB 34.5 and 36.6 us
-// (bf16), 101 MB 25.1 and 33.0 (fp32); 117 MB 50.1 and 39.7; 134 MB 61.9 and
-// 44.3.
-constexpr int64_t kLargeBytes = (int64_t)104 << 20;
-bool large_batch(bool bf16, int32_t B, int32_t V) { return (int64_t)B * V * (bf16 ? 2 : 4) > kLargeBytes; }
+// (mask_tile) rather than stored to.  Storing is the shorter way while the
+// batch's partial lines are in the 256 MB Infinity Cache and the longer one
+// when they are not, which depends on what else the program touches between
+// two calls, and a call cannot know that.  The line lies where storing stops
+// being the better one for up to four logits buffers of the batch's size used
+// in turn with nothing else between; fp32 batches have fewer partial lines to
+// their size.  us of the step, 262,144 tokens, dense masks of a programming
+// language, stores / this / the kernel before both (16-byte vectors read,
+// selected and written); `fresh`: a kernel has just written the logits,
+// through one buffer or through four:
+//                  1 buffer          3 in turn         4                 8                 fresh, 1          fresh, 4
+//   bf16  67 MB    16.7/20.9/27.8    16.6/20.7/27.9    18.4/20.7/27.7    33.5/21.3/27.8    17.0/19.0/26.2    19.3/19.0/25.4
+//         92 MB    21.2/26.9/35.3    24.1/26.9/35.0    36.7/27.0/35.1    44.1/28.2/34.8    21.3/23.5/32.2    22.7/23.4/31.4
+//        100 MB    22.8/29.6/38.3    28.0/29.4/38.2    45.8/29.6/38.3    47.8/31.4/38.1    23.2/26.2/35.1    25.6/25.7/33.7
+//        134 MB    29.1/38.3/50.3    56.7/37.9/49.9    63.5/38.6/49.9    63.4/48.1/50.0    29.3/33.7/45.7    36.1/34.4/43.8
+//   fp32  84 MB    17.9/24.0/34.2    17.8/24.0/34.3    22.3/23.9/34.2    38.7/25.2/34.2    18.4/20.7/31.0    18.2/20.1/30.2
+//        104 MB    21.7/29.2/41.0    25.4/29.1/41.3    42.2/29.0/41.0    47.3/32.7/40.9    22.1/25.2/37.8    24.3/25.3/36.2
+//        134 MB    25.8/34.9/50.3    44.3/34.8/50.2    58.7/35.1/50.3    59.3/43.6/50.2    26.1/29.9/46.5    32.5/30.6/44.2
+// So up to four buffers no size is more than 5% slower than the kernel before
+// both, and with any number none by more than 27%; above the line the select
+// costs up to 37% over stores on one buffer that nothing evicts.  (Rows off
+// whole mask words were stored to by element before: above the line fp32 rows
+// take up to 21% longer than that on one buffer and 7% longer freshly written,
+// 27% less on three in turn.)
+constexpr int64_t kLargeBytesBf16 = (int64_t)88 << 20, kLargeBytesF32 = (int64_t)100 << 20;
+bool large_batch(bool bf16, int32_t B, int32_t V) {
+    return (int64_t)B * V * (bf16 ? 2 : 4) > (bf16 ? kLargeBytesBf16 : kLargeBytesF32);
+}
 
 // Whether the step masks rows of V logits an element per thread: below 6 KiB
 // they fill no more than one and a half of a workgroup's four tiles, and a
@@ -1872,7 +1893,7 @@ void launch_fast_dtype(bool spec, bool sliced, bool tl, const FastArgs &F) {
 psc_status launch_fused(const psc_handle *h, const int32_t *stacks, int32_t stride, int64_t n_stack,
                         const int32_t *stack_lens, const int32_t *lexer_states, int32_t B, uint32_t *out_bitmask,
                         void *logits, psc_dtype dtype, int32_t V, void *stream, const char *what,
-                        unsigned long long *tl = nullptr, int64_t n_tl = 0, bool buffer_per_step = false) {
+                        unsigned long long *tl = nullptr, int64_t n_tl = 0) {
     // out_bitmask may be null: the logits stand in for it in the null check
     if (psc_status st = check_states(h, stacks, stride, n_stack, stack_lens, lexer_states, B,
                                      out_bitmask ? static_cast<const void *>(out_bitmask) : logits, what))
@@ -1898,7 +1919,7 @@ psc_status launch_fused(const psc_handle *h, const int32_t *stacks, int32_t stri
         const unsigned segments = spec ? (W + fused_words_per_block(bf16) - 1) / fused_words_per_block(bf16)
                                        : (tiles_of(logits, bf16, V) + per - 1) / per;
         const FastArgs F{dim3(segments, B), s, T, h->n_lex, h->n_lr, h->n_classes, stacks, stride, n_stack, stack_lens,
-                         lexer_states, W, out_bitmask, logits, V, buffer_per_step || large_batch(bf16, B, V), tl};
+                         lexer_states, W, out_bitmask, logits, V, large_batch(bf16, B, V), tl};
         if (bf16) launch_fast_dtype<true>(spec, T.sliced, tl != nullptr, F);
         else launch_fast_dtype<false>(spec, T.sliced, tl != nullptr, F);
     } else {
@@ -2452,10 +2473,15 @@ extern "C" psc_status psc_decode_step(const psc_handle *h, const int32_t *stacks
         hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return device_fail(what, e0);
         return launch_fused(h, stacks_out, cap, kUnbounded, lens_out, qs_out, B, out_bitmask, logits, dtype, V, stream,
-                            what, nullptr, 0, true);
+                            what);
     }
     const dim3 grid((unsigned)segments, B);
     if (fast) {
+        // Densely mixed tiles are read, selected and written at every size of a
+        // single launch (up to 33 MB): us, stores / select, 16.4 MB bf16 11.0 /
+        // 11.4 on three buffers in turn, 9.7 / 9.4 freshly written, 12.0 / 9.7 on
+        // 32; 33.5 MB 16.2 / 17.1, 15.9 / 16.0 and 22.1 / 19.4; 33 MB fp32 14.3 /
+        // 15.8, 13.8 / 14.2 and 18.6 / 16.8.
 #define PSC_DECODE_FAST(BF, SL, PL)                                                                                    \
     hipLaunchKernelGGL((decode_fast_kernel<BF, SL, PL>), grid, dim3(kFusedBlock), 0, s, T.table, T.masks, T.mstride,  \
                        T.ids, D, V, W, 1, out_bitmask, T.err, logits)

@@ -8,7 +8,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
-from paper_2608_03065_amd.psc import Classifier, apply_mask, pack_states  # noqa: E402
+from paper_2608_03065_amd.psc import Classifier, DecodeStates, apply_mask, pack_states  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -61,10 +61,13 @@ def test_apply_around_the_small_batch_limit(dtype, B, V):
 
 
 @pytest.mark.parametrize("dtype,B,V,offset", [(torch.bfloat16, 28, 2000001, 5), (torch.bfloat16, 27, 2097152, 0),
-                                              (torch.float32, 27, 1050001, 3)])
+                                              (torch.float32, 27, 1050001, 3), (torch.bfloat16, 22, 2097152, 0),
+                                              (torch.bfloat16, 23, 2097152, 64), (torch.bfloat16, 24, 2000003, 1),
+                                              (torch.float32, 25, 1048576, 0), (torch.float32, 26, 1048577, 1)])
 def test_large_batch_dense_and_sparse(dtype, B, V, offset):
-    """Above 104 MiB of logits: dense rows are read, selected and written,
-    sparse ones and the first and last tiles of a row are stored."""
+    """Above 88 (bf16) and 100 (fp32) MiB of logits dense rows are read,
+    selected and written, sparse ones and the first and last tiles of a row are
+    stored; batches of those sizes and just past them."""
     W = (V + 31) // 32
     bits = _mixed_bits(B, W, 3)
     dense = torch.randint(-2**31, 2**31, (B // 2, W), device=DEV, dtype=torch.int64).to(torch.int32)
@@ -118,3 +121,35 @@ def test_step_rows_around_the_element_limit(dtype, V, layout):
         out = torch.empty_like(bits)
         clf.compute_and_apply(*pack_states(states, DEV), buf.view(dtype)[offset:offset + n].view(-1, V), out=out)
         assert torch.equal(buf, want) and torch.equal(out, bits), offset
+
+
+@pytest.mark.parametrize("dtype,B", [(torch.bfloat16, 219), (torch.bfloat16, 220), (torch.float32, 124),
+                                     (torch.float32, 125)])
+def test_step_of_large_batches(dtype, B):
+    """The step and the decoding step (two launches) on either side of the size
+    from which dense tiles are read, selected and written, rows of 210,001 at
+    an odd offset, masks dense (every token or two of three) and sparse."""
+    V = 210001
+
+    class Vocab:
+        tokens = [b"%d" % (10 + i) if i % 3 else b"x%d" % i for i in range(V - 1)] + [b""]
+        eos_id = V - 1
+    clf = Classifier.from_text('%start v\nN: /[0-9]+/\nS: /"[a-z0-9]*"/\nv: N | S\n', Vocab).bind(DEV)
+    kinds = [clf.host_state(t) for t in (b"", b'"', b"12", b'"a"')]
+    states = [kinds[b % 4] for b in range(B)]
+    bits = torch.from_numpy(clf.masks_host(kinds).view("int32")).to(DEV)
+    shift = torch.arange(32, device=DEV, dtype=torch.int32)
+    masked = ~((bits[:, :, None] >> shift) & 1).bool().flatten(1)[:, :V]
+    bits, masked = bits[torch.arange(B) % 4], masked[torch.arange(B) % 4]
+    ints = torch.int16 if dtype == torch.bfloat16 else torch.int32
+    inf = torch.tensor(float("-inf"), dtype=dtype).view(ints).item()
+    old = torch.randint(-2**15, 2**15, (B * V + 81,), device=DEV, dtype=torch.int32).to(ints)
+    want = old.clone()
+    want[1:1 + B * V].view(B, V).masked_fill_(masked, inf)
+    ds = DecodeStates(clf, B, 16, DEV).load(states)
+    skip = torch.full((B,), -1, dtype=torch.int32, device=DEV)
+    for call in (lambda lg, out: clf.compute_and_apply(*pack_states(states, DEV), lg, out=out),
+                 lambda lg, out: ds.decode_step(skip, lg, out=out)):
+        buf, out = old.clone(), torch.empty_like(bits)
+        call(buf.view(dtype)[1:1 + B * V].view(B, V), out)
+        assert torch.equal(buf, want) and torch.equal(out, bits)
