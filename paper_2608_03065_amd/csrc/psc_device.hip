@@ -2065,10 +2065,10 @@ AdvTables adv_tables(const psc_handle *h) {
                      h->has_closure ? reinterpret_cast<const i32x2 *>(base + h->closure_off) : nullptr};
 }
 
-// Workgroups of 256 threads that fit on the current GPU at once: 8 per
-// compute unit (4 SIMDs x 8 wavefronts; the fused kernels' registers allow
-// it), from the device's compute-unit count.
-int64_t resident_blocks() { return (int64_t)compute_units() * 8; }
+// Workgroups of the decoding step that are on the current GPU at once, 4 SIMDs
+// x 8 wavefronts a compute unit, or x 7 where the tables are not of the plain
+// forms (the kernels then need more scalar registers).
+int64_t resident_blocks(bool plain) { return (int64_t)compute_units() * (plain ? 8 : 7); }
 
 // Rows of V logits that one launch of the apply takes: their elements are
 // counted in 31 bits where the rows are masked as one long row (whole mask
@@ -2467,7 +2467,7 @@ extern "C" psc_status psc_decode_step(const psc_handle *h, const int32_t *stacks
     // fused step follows on the new states (same results).
     const int waves = kFusedBlock / kWave;
     const int64_t segments = fast ? (tiles_of(logits, bf16, V) + waves - 1) / waves : (W + kGenWords - 1) / kGenWords;
-    if (segments * B > resident_blocks()) {
+    if (segments * B > resident_blocks(D.T.plain())) {
         if (D.T.plain()) hipLaunchKernelGGL(advance_copy_kernel<true>, dim3(B), dim3(kWave), 0, s, D);
         else hipLaunchKernelGGL(advance_copy_kernel<false>, dim3(B), dim3(kWave), 0, s, D);
         hipError_t e0 = hipGetLastError();

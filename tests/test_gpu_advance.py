@@ -436,3 +436,30 @@ def test_decode_step_by_elements_and_by_tiles(dtype, V, B, layout):
             allowed = ((bits[b0:b0 + 256, :, None] >> shift) & 1).bool().flatten(1)[:, :V]
             rows[b0:b0 + 256].masked_fill_(~allowed, inf)
         assert torch.equal(out, bits) and torch.equal(buf, want), k
+
+
+@pytest.mark.parametrize("B", [1792, 1793, 2048, 2049])
+def test_decode_step_of_long_productions(B):
+    """Tables with a production too long for packed reductions, batches around
+    the two-launch form's (7 or 8 workgroups per compute unit, 256 of them):
+    the decoding step against psc_advance followed by the step."""
+    text = '%start s\nN: /[0-9]+/\ns: e | s ";" e\ne: N | "(" e ")" | "#" ' + '"~" ' * 260
+
+    class Vocab:
+        tokens = [b"%d" % i for i in range(60)] + [b"(", b")", b";", b"#" + b"~" * 130, b"~" * 130, b"~", b""]
+        eos_id = 66
+    clf = psc.Classifier.from_text(text + "\n", Vocab).bind(DEV)
+    a, r = (DecodeStates(clf, B, 300, DEV) for _ in range(2))
+    plans = [[60, 3, 61, 62], [63, 64, 62, 5], [7, 62, 63, 65], [60, 60, 4, 61], [8, 66, 66, -1]]
+    for k in range(4):
+        t = torch.tensor([plans[b % 5][k] for b in range(B)], dtype=torch.int32, device=DEV)
+        l1 = torch.randn(B, clf.V, device=DEV)
+        l2 = l1.clone()
+        o1, o2 = (torch.empty((B, clf.W), dtype=torch.int32, device=DEV) for _ in range(2))
+        s1, s2 = a.decode_step(t, l1, out=o1).clone(), r.advance(t).clone()
+        r.compute_and_apply(l2, out=o2)
+        assert torch.equal(s1, s2) and torch.equal(o1, o2) and torch.equal(l1, l2), k
+        assert _same_states(a.host_states(), r.host_states()) < 0, k
+        want = [clf.host_state(b"".join(Vocab.tokens[t] for t in p)) for p in
+                ([plans[b][i] for i in range(k + 1) if plans[b][i] < 66] for b in range(5))]
+        assert _same_states(a.host_states()[:5], want) < 0, k
