@@ -784,6 +784,21 @@ apply_fast_kernel(void *__restrict__ logits, const uint32_t *__restrict__ bits, 
 constexpr int32_t kShortRow = 512;
 constexpr int64_t kSmallBytes = (int64_t)3 << 19;
 
+// Element i of the logits, at any byte address.
+template <bool kBf16>
+__device__ __forceinline__ void put_inf(void *logits, size_t i) {
+    if (kBf16) __builtin_memcpy(static_cast<char *>(logits) + i * 2, &kBf16NegInf, 2);
+    else __builtin_memcpy(static_cast<char *>(logits) + i * 4, &kF32NegInf, 4);
+}
+
+// Its float bits.
+template <bool kBf16>
+__device__ __forceinline__ uint32_t get_bits(const void *logits, size_t i) {
+    uint32_t u = 0;
+    __builtin_memcpy(&u, static_cast<const char *>(logits) + i * (kBf16 ? 2 : 4), kBf16 ? 2 : 4);
+    return kBf16 ? u << 16 : u;
+}
+
 template <bool kBf16, class Index>
 __global__ void __launch_bounds__(kBlock)
 apply_generic_kernel(void *__restrict__ logits, const uint32_t *__restrict__ bits, Index n, int32_t V, int32_t W) {
@@ -791,8 +806,7 @@ apply_generic_kernel(void *__restrict__ logits, const uint32_t *__restrict__ bit
         const Index b = e / (Index)V;
         const int32_t v = (int32_t)(e - b * (Index)V);
         if ((bits[(int64_t)b * W + (v >> 5)] >> (v & 31)) & 1u) continue;
-        if (kBf16) reinterpret_cast<uint16_t *>(logits)[e] = kBf16NegInf;
-        else reinterpret_cast<uint32_t *>(logits)[e] = kF32NegInf;
+        put_inf<kBf16>(logits, e);
     }
 }
 
@@ -888,8 +902,7 @@ __device__ __forceinline__ void fused_generic_apply(int cls, int b, const uint32
     for (int e = e0 + threadIdx.x; e < e1; e += kBlock) {
         if ((s_m[(e - e0) >> 5] >> (e & 31)) & 1u) continue;
         const size_t idx = (size_t)b * V + e;
-        if (kBf16) reinterpret_cast<uint16_t *>(logits)[idx] = kBf16NegInf;
-        else reinterpret_cast<uint32_t *>(logits)[idx] = kF32NegInf;
+        put_inf<kBf16>(logits, idx);
     }
 }
 
@@ -1284,10 +1297,7 @@ argmax_partial_kernel(const int32_t *__restrict__ table, const uint32_t *__restr
             const int v_end = (int)min((int64_t)V, ((int64_t)blockIdx.x + 1) * kGenWords * 32);
             for (int v = blockIdx.x * kGenWords * 32 + threadIdx.x; v < v_end; v += kFusedBlock) {
                 if (!((*mask_at<kSliced>(masks, mask_stride, ids, cls, v >> 5) >> (v & 31)) & 1u)) continue;
-                const size_t idx = (size_t)b * V + v;
-                const uint32_t f = kBf16 ? (uint32_t)reinterpret_cast<const uint16_t *>(logits)[idx] << 16
-                                         : reinterpret_cast<const uint32_t *>(logits)[idx];
-                best = umax64(best, arg_key(f, v));
+                best = umax64(best, arg_key(get_bits<kBf16>(logits, (size_t)b * V + v), v));
             }
             best = wave_umax64(best);
         }

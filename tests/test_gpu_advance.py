@@ -218,8 +218,7 @@ def test_decode_step_equals_advance_then_step(built, name, B, steps, dtype, offs
     states, bitmask and masked logits identical at every step; tokens mix
     allowed ones, EOS, skips and (every fifth step) random ones.  The stress
     shapes (more workgroups than fit on the GPU at once) take the two-launch
-    form of the call, on the fast path and, with misaligned logits, on the
-    general one."""
+    form of the call, with logits at 16 bytes and off them."""
     wl, clf, orc = built(name)
     rng = np.random.default_rng(7)
     cap = 512

@@ -49,7 +49,7 @@ def test_argmax_matches_closed_form(built, name, steps):
                                           (torch.bfloat16, 3)])
 def test_argmax_special_values(built, dtype, offset):
     """NaN, infinities, signed zeros, ties and rows whose allowed logits are
-    all -inf, on the fast (aligned) and the general path."""
+    all -inf, on rows that start at 16-byte vectors and rows that do not."""
     wl, clf, orc = built("json")
     states = wl.states(12)
     B, V = len(states), wl.V
@@ -129,7 +129,7 @@ def test_greedy_decoding_on_device(built, name, B, steps):
 
 def test_argmax_calls_in_a_row_leave_no_state(built):
     """The per-sequence slots and arrival counters are cleared by each call:
-    a full batch, a smaller one, the general path and the full batch again,
+    a full batch, a smaller one, one off 16 bytes and the full batch again,
     back to back on one stream, each against the closed form."""
     wl, clf, orc = built("schema")
     cases = [(wl.states(40), 0), (wl.states(41)[:5], 0), (wl.states(42)[:9], 1), (wl.states(43), 0)]

@@ -57,13 +57,13 @@ def test_fused_step_bit_exact(built, name, steps):
 
 
 @pytest.mark.parametrize("name,dtype,offset", [
-    ("arithmetic", torch.bfloat16, 0),   # V = 513: general path
-    ("json", torch.bfloat16, 0),         # V = 32000: fast path, the other dtype
-    ("json", torch.float32, 1),          # misaligned logits: general path
-    ("schema", torch.float32, 0),        # fast path, fp32
-    ("schema", torch.bfloat16, 3),       # misaligned bf16: general path
-    ("stress", torch.float32, 0),        # fast path, fp32, 16,384 workgroups
-    ("stress", torch.bfloat16, 1)])      # general path, 16,384 workgroups
+    ("arithmetic", torch.bfloat16, 0),   # V = 513: a short row, an element per thread
+    ("json", torch.bfloat16, 0),         # V = 32000: tiles, the other dtype
+    ("json", torch.float32, 1),          # tiles of rows off 16 bytes
+    ("schema", torch.float32, 0),        # tiles, fp32
+    ("schema", torch.bfloat16, 3),       # tiles of rows off 16 bytes, bf16
+    ("stress", torch.float32, 0),        # tiles, fp32, 16,384 workgroups
+    ("stress", torch.bfloat16, 1)])      # tiles of rows off 16 bytes, 8,448 workgroups
 def test_fused_other_dtype_and_alignment(built, name, dtype, offset):
     wl, clf, orc = built(name)
     states = wl.states(9)

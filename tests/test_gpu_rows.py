@@ -1,13 +1,15 @@
 """GPU parity of the masking of logits rows at every alignment: a row is cut
 at 128-byte lines of memory into 4 KiB tiles, so its first and last tile, the
 lines at their ends, lines masked whole and lines left alone are the cases;
-large batches read, select and write densely mixed tiles instead.  Compared
-bit for bit with the closed form on the same bits (the apply only copies or
+large batches read, select and write densely mixed tiles instead; short rows,
+small batches and logits off their own alignment are masked an element per
+thread.  Compared bit for bit with the closed form on the same bits (the apply only copies or
 writes -inf)."""
 import pytest
 
 torch = pytest.importorskip("torch")
 
+from paper_2608_03065_amd import psc  # noqa: E402
 from paper_2608_03065_amd.psc import Classifier, DecodeStates, apply_mask, pack_states  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -153,3 +155,54 @@ def test_step_of_large_batches(dtype, B):
         buf, out = old.clone(), torch.empty_like(bits)
         call(buf.view(dtype)[1:1 + B * V].view(B, V), out)
         assert torch.equal(buf, want) and torch.equal(out, bits)
+
+
+@pytest.mark.parametrize("dtype,skew", [(torch.bfloat16, 1), (torch.float32, 1), (torch.float32, 2)])
+@pytest.mark.parametrize("V,B", [(33, 70), (513, 2500), (5001, 40), (5001, 1100), (40001, 9)])
+def test_logits_off_their_own_alignment(V, B, dtype, skew):
+    """Logits at a byte address that is no multiple of their element's size, as
+    only a C caller can hand over: the apply, the step, both forms of the
+    decoding step (batches of at most 2,048 workgroups and larger ones) and the
+    argmax, an element per thread at every size."""
+    class Vocab:
+        tokens = [b"%d" % (10 + i) if i % 3 else b"x%d" % i for i in range(V - 1)] + [b""]
+        eos_id = V - 1
+    clf = Classifier.from_text('%start v\nN: /[0-9]+/\nS: /"[a-z0-9]*"/\nv: N | S\n', Vocab).bind(DEV)
+    kinds = [clf.host_state(t) for t in (b"", b'"', b"12", b'"a"')]
+    states = [kinds[b % 4] for b in range(B)]
+    bits = torch.from_numpy(clf.masks_host(kinds).view("int32")).to(DEV)[torch.arange(B) % 4]
+    item, code = (2, psc.PSC_BF16) if dtype == torch.bfloat16 else (4, psc.PSC_F32)
+    ints = torch.int16 if dtype == torch.bfloat16 else torch.int32
+    shift = torch.arange(32, device=DEV, dtype=torch.int32)
+    allowed = ((bits[:, :, None] >> shift) & 1).bool().flatten(1)[:, :V]
+    x = torch.randn(B, V, device=DEV).to(dtype)
+    want = x.masked_fill(~allowed, float("-inf"))
+    packed = pack_states(states, DEV)
+    ds, spare = DecodeStates(clf, B, 16, DEV).load(states), DecodeStates(clf, B, 16, DEV)
+    skip = torch.full((B,), -1, dtype=torch.int32, device=DEV)
+    out, toks = torch.empty_like(bits), torch.empty(B, dtype=torch.int32, device=DEV)
+    ptr = lambda *ts: [t.data_ptr() for t in ts]
+    st, n = ptr(*packed), B * V * item
+    calls = {
+        "apply": lambda p: psc.lib().psc_apply_mask(p, code, bits.data_ptr(), B, V, None),
+        "step": lambda p: psc.lib().psc_compute_and_apply(clf._h, *st, B, out.data_ptr(), p, code, V, None),
+        "decode": lambda p: psc.lib().psc_decode_step(
+            clf._h, *ptr(ds.stacks, ds.lens, ds.qs, spare.stacks, spare.lens, spare.qs), 16, B,
+            *ptr(skip, ds.status, out), p, code, V, None),
+        "argmax": lambda p: psc.lib().psc_compute_and_argmax(clf._h, *st, B, p, code, V, toks.data_ptr(), None)}
+    for name, call in calls.items():
+        buf = torch.full((skew + n + 64,), 0x5A, dtype=torch.uint8, device=DEV)
+        buf[skew:skew + n] = x.view(torch.uint8).flatten()
+        out.zero_()
+        torch.cuda.synchronize()
+        psc._check(call(buf.data_ptr() + skew))
+        torch.cuda.synchronize()
+        got = buf[skew:skew + n].clone().view(ints).view(B, V)
+        assert torch.equal(got, (x if name == "argmax" else want).view(ints)), name
+        assert (buf[:skew] == 0x5A).all() and (buf[skew + n:] == 0x5A).all(), name
+        if name in ("step", "decode"):
+            assert torch.equal(out, bits), name
+    f = want.float()
+    best = f.max(1, keepdim=True).values
+    first = torch.where((f == best) & allowed, torch.arange(V, device=DEV), V).amin(1)
+    assert torch.equal(toks.long(), torch.where(allowed.any(1), first, -1))
