@@ -353,9 +353,9 @@ def main():
         t_copy = graph_loop(copy)
 
         # the apply kernel's floors at this shape: an all-zero bitmask (every
-        # vector one store of -inf, no logits read) and an all-one bitmask
-        # (no logits touched: the launch and the bitmask read); beside
-        # apply_mask_solo they show what reading the mixed vectors costs
+        # line stored whole) and an all-one bitmask (no logits touched: the
+        # launch and the bitmask read); beside apply_mask_solo they show what
+        # the partly masked lines cost
         bm_const = {"all_masked": torch.zeros((B, W), dtype=torch.int32, device=dev),
                     "all_allowed": torch.full((B, W), -1, dtype=torch.int32, device=dev)}
         t_apply_floor = {}
@@ -373,30 +373,19 @@ def main():
         # step on them (psc_compute_and_apply_dense)
         decode = decode_steps(wl, clf, B, pool, bms, stream, dev, args.decode_steps)
 
-    # Algorithmic bytes, from the actual masks.  The apply touches logits per
-    # 16-byte vector: one whose entries are all masked is written once
-    # (16 B); one that keeps some entries and masks others must be read to be
-    # written (32 B); one that keeps all entries is not touched.  (V % 32 == 0
-    # here, so vectors never straddle rows.)  The walk reads the stacks, lens
-    # and states; the gather reads the class's mask row and writes the
-    # bitmask (4 W B each); the two-launch apply reads the bitmask back.
-    per_vec = 16 // s_logit
+    # Algorithmic bytes, from the actual masks.  Masking needs no old value:
+    # each masked logit is written once, and a kept one is not touched.  The
+    # walk reads the stacks, lens and states; the gather reads the class's mask
+    # row and writes the bitmask (4 W B each); the two-launch apply reads the
+    # bitmask back.  (Batches large enough for their dense tiles to be read,
+    # selected and written move more than this.)
     logit_bytes, stack_total = [], 0
     for s in range(n_distinct):
         stacks, lens, qs = step_inputs[s]
         clf.compute_masks(stacks, lens, qs, out=bms[0], stream=stream)
         torch.cuda.synchronize()
-        m = bms[0].cpu().numpy().view(np.uint32)
-        if per_vec == 8:
-            groups = m.view(np.uint8).reshape(-1)
-            full = 0xFF
-        else:
-            b8 = m.view(np.uint8).reshape(-1)
-            groups = np.stack([b8 & 0xF, b8 >> 4], axis=1).reshape(-1)
-            full = 0xF
-        n_masked = int((groups == 0).sum())
-        n_mixed = int(((groups != 0) & (groups != full)).sum())
-        logit_bytes.append(16 * n_masked + 32 * n_mixed)
+        kept = int(np.bitwise_count(bms[0].cpu().numpy().view(np.uint32)).sum(dtype=np.int64))   # bits past V are 0
+        logit_bytes.append(s_logit * (B * V - kept))
         stack_total += int(lens.sum().item())
     stack_words = stack_total / n_distinct
     bytes_walk_gather = 4 * stack_words + 8 * B + 2 * 4 * W * B
@@ -409,32 +398,32 @@ def main():
     masks_per_s = B / (ms_per_step * 1e-3)
     bytes_apply_solo = 4 * W * B + float(np.mean(logit_bytes[:n_bm]))
     achieved_apply = bytes_apply_solo / (t_apply * 1e-6) / 1e9
-    fast = V % 32 == 0
+    step_kernel, apply_kernel = kernels_of(B, V, s_logit, args.speculate)
     if args.mode == "fused":
-        kname = ("fused_spec_kernel" if args.speculate else "fused_fast_kernel") if fast else "fused_generic_kernel"
+        kname = step_kernel
         achieved = bytes_fused / (lat_us * 1e-6) / 1e9
         roofline = {
             "bound": "hbm", "kernel": kname,
             "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": measured_traffic(wl, kname) if fast else None,
+            "traffic": measured_traffic(wl, kname),
             "algorithmic_bytes_per_launch": round(bytes_fused),
             "avg_launch_us": round(lat_us, 3),
             "timing": "HIP events on the bench stream around the timed loop; one launch per step",
             # the read-every-logit-and-write-it-back byte model, for comparison
-            # only: the kernel does not move these bytes (fully masked vectors
-            # are only written, kept ones not touched)
+            # only: the kernel does not move these bytes (masked logits are only
+            # written, kept ones not touched)
             "one_pass_model": {"bytes": round(one_pass_model),
                                "gbs": round(one_pass_model / (lat_us * 1e-6) / 1e9, 1),
                                "frac": round(one_pass_model / (lat_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4)},
         }
     else:
-        kname = "apply_fast_kernel" if fast else "apply_generic_kernel"
+        kname = apply_kernel
         roofline = {
             "bound": "hbm", "kernel": kname,
             "achieved": round(achieved_apply, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved_apply / HBM_PEAK_GBS, 4),
-            "traffic": measured_traffic(wl, kname) if fast else None,
+            "traffic": measured_traffic(wl, kname),
             "algorithmic_bytes_per_launch": round(bytes_apply_solo),
             "avg_launch_us": round(t_apply, 3),
             "timing": "HIP events around 1000 back-to-back launches of the kernel alone on the bench stream",
@@ -446,7 +435,7 @@ def main():
     ach_two = bytes_two_launch / (t_two * 1e-6) / 1e9
     roofline_two = {
         "calls": "psc_compute_masks + psc_apply_mask (two launches, one stream)",
-        "bound": "hbm", "kernels": ["walk_gather_kernel", "apply_fast_kernel" if fast else "apply_generic_kernel"],
+        "bound": "hbm", "kernels": ["walk_gather_kernel", apply_kernel],
         "achieved": round(ach_two, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": round(ach_two / HBM_PEAK_GBS, 4), "algorithmic_bytes_per_step": round(bytes_two_launch),
         "step_us": round(t_two, 3),
@@ -675,6 +664,18 @@ def workload_fingerprint(wl) -> str:
     g = wl.grammar
     key = f"{wl.name}|{g.n_terminals}|{g.n_nonterminals}|{g.n_lr_states}|{len(g.productions)}|{wl.V}|{wl.B}"
     return hashlib.sha256(key.encode()).hexdigest()[:16]
+
+
+def kernels_of(B: int, V: int, item: int, speculate: bool):
+    """The kernels of the single-launch step and of the mask application for
+    logits [B, V] of `item` bytes, by the library's rules: tiles, or an element
+    per thread for rows below 6 KiB (step), rows below 512 and batches below
+    1.5 MiB (application; rows of whole mask words count as one)."""
+    step = "fused_fast_kernel" if V * item >= 6 << 10 else "fused_generic_kernel"
+    if speculate and V % 32 == 0:
+        step = "fused_spec_kernel"
+    row = B * V if V % 32 == 0 else V
+    return step, "apply_fast_kernel" if row >= 512 and B * V * item >= 3 << 19 else "apply_generic_kernel"
 
 
 def measured_traffic(wl, kernel: str):

@@ -1391,6 +1391,8 @@ __device__ __forceinline__ int64_t feed_step_bound(int32_t n_nt, int len, int ca
 // other; eight decoding steps of 64 x 128,256 bf16 89 against 94.  Lexing 8 or
 // 16 bytes at once, from their columns of the lexer's table in registers, was
 // no faster (5.3 and 5.2): the unrolled code took what the loads no longer did.
+// The action beside the closure's state is 0.15 us of that difference (4.7 us an
+// advance without it, 4.55 with, 5.6 before) for twice the closure's bytes.
 //
 // advance_core computes the outcome of token `tok` on the state (q_in, st
 // of `len` symbols, at most `cap`) and writes nothing but the overlay: on

@@ -40,3 +40,15 @@ def test_fingerprints_tell_the_workloads_apart():
     fps = {bench.workload_fingerprint(configs.get(n)) for n in ("arithmetic", "json", "schema", "pylike",
                                                                 "stress", "gosql")}
     assert len(fps) == 6
+
+
+def test_kernels_named_by_the_librarys_rules():
+    assert bench.kernels_of(64, 151936, 2, False) == ("fused_fast_kernel", "apply_fast_kernel")
+    assert bench.kernels_of(64, 151936, 2, True)[0] == "fused_spec_kernel"
+    assert bench.kernels_of(64, 151665, 2, True)[0] == "fused_fast_kernel"      # speculation: whole mask words only
+    assert bench.kernels_of(8, 513, 4, False) == ("fused_generic_kernel", "apply_generic_kernel")
+    assert bench.kernels_of(4000, 480, 2, False) == ("fused_generic_kernel", "apply_fast_kernel")
+    assert bench.kernels_of(4000, 481, 2, False)[1] == "apply_generic_kernel"
+    src = open(os.path.join(ROOT, "paper_2608_03065_amd", "csrc", "psc_device.hip")).read()
+    for rule in ("kStepShortRow = 6 << 10;", "kShortRow = 512;", "kSmallBytes = (int64_t)3 << 19;"):
+        assert rule in src
