@@ -360,10 +360,12 @@ psc_status psc_predictor_fill(const psc_handle *h, int32_t cls, void *stream);
  * Options of a handle's device calls (a bitwise OR; 0 = the defaults):
  *  PSC_OPT_SPECULATE  psc_compute_and_apply loads the predicted class's mask
  *                     words and partly allowed logits during the walk (the
- *                     class predictor above); results are identical either
- *                     way.  Off by default: on MI355X the walk's loads and
- *                     the workgroup's second barrier cost about what the
- *                     early loads save.
+ *                     class predictor above), where V is a multiple of 32 and
+ *                     the logits are 16-byte aligned (elsewhere the option
+ *                     changes nothing); results are identical either way.
+ *                     Off by default: on MI355X the walk's loads and the
+ *                     workgroup's second barrier cost more than the early
+ *                     loads save.
  * Errors: PSC_E_INVALID_ARG (null handle, unknown option).
  */
 enum { PSC_OPT_SPECULATE = 1 };

@@ -1832,6 +1832,11 @@ int32_t tiles_of(const void *logits, bool bf16, int32_t V) {
 //   fp32  84 MB    17.9/24.0/34.2    17.8/24.0/34.3    22.3/23.9/34.2    38.7/25.2/34.2    18.4/20.7/31.0    18.2/20.1/30.2
 //        104 MB    21.7/29.2/41.0    25.4/29.1/41.3    42.2/29.0/41.0    47.3/32.7/40.9    22.1/25.2/37.8    24.3/25.3/36.2
 //        134 MB    25.8/34.9/50.3    44.3/34.8/50.2    58.7/35.1/50.3    59.3/43.6/50.2    26.1/29.9/46.5    32.5/30.6/44.2
+// Right after what writes logits in a model, the step takes, stores / select /
+// the kernel before (events around it, 3 us of them): after the output
+// projection (K = 4,096, whose weights pass the cache) 33 MB bf16 18.3 / 19.6 /
+// 19.6, 87 MB 37.2 / 38.4 / 39.9; after its cast to fp32 66 MB 28.0 / 30.6 /
+// 30.3, 174 MB 61.2 / 66.4 / 65.9.
 // So up to four buffers no size is more than 5% slower than the kernel before
 // both, and with any number none by more than 27%; above the line the select
 // costs up to 37% over stores on one buffer that nothing evicts.  (Rows off
