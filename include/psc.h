@@ -386,8 +386,9 @@ psc_status psc_predictor_updates(const psc_handle *h, uint32_t *out, int32_t res
  *   [2] (its last store issued) - start, then, << 32: wavefront | XCD << 3 |
  *       prediction held << 7 | class known at the first step << 8;
  *   [3] sequence | slice << 32.
- * Results are those of psc_compute_and_apply_n.  Fast path only
- * (V % 32 == 0, 16-byte aligned logits): PSC_E_INVALID_ARG otherwise.
+ * Results are those of psc_compute_and_apply_n.  V % 32 == 0 and 16-byte
+ * aligned logits only: PSC_E_INVALID_ARG otherwise.  Rows below 6 KiB, which
+ * the step itself masks an element per thread, are masked by tiles here.
  */
 int64_t psc_timeline_records(const psc_handle *h, int32_t B, psc_dtype dtype);
 psc_status psc_compute_and_apply_timeline(const psc_handle *h, const int32_t *stacks, int64_t n_stack,

@@ -840,8 +840,8 @@ __host__ __device__ constexpr int32_t timeline_slices(int32_t W) {
 }
 
 // A timeline record per wavefront (psc_compute_and_apply_timeline) of a
-// sequence's first `slices` workgroups: its start, the prediction known (t_a), its class known (t_b) and its last
-// store issued, in ticks of the GPU's constant 100 MHz clock; then the
+// sequence's first `slices` workgroups: its start, the prediction known (t_a),
+// its class known (t_b) and its last store issued, in ticks of the GPU's constant 100 MHz clock; then the
 // wavefront, its XCD, whether the prediction held and whether the class was
 // known at the first step; then the sequence and the slice.
 __device__ __forceinline__ void timeline_record(unsigned long long *__restrict__ tl, uint32_t slices,
@@ -1824,14 +1824,14 @@ int32_t tiles_of(const void *logits, bool bf16, int32_t V) {
 // language, stores / this / the kernel before both (16-byte vectors read,
 // selected and written); `fresh`: a kernel has just written the logits,
 // through one buffer or through four:
-//                  1 buffer          3 in turn         4                 8                 fresh, 1          fresh, 4
-//   bf16  67 MB    16.7/20.9/27.8    16.6/20.7/27.9    18.4/20.7/27.7    33.5/21.3/27.8    17.0/19.0/26.2    19.3/19.0/25.4
-//         92 MB    21.2/26.9/35.3    24.1/26.9/35.0    36.7/27.0/35.1    44.1/28.2/34.8    21.3/23.5/32.2    22.7/23.4/31.4
-//        100 MB    22.8/29.6/38.3    28.0/29.4/38.2    45.8/29.6/38.3    47.8/31.4/38.1    23.2/26.2/35.1    25.6/25.7/33.7
-//        134 MB    29.1/38.3/50.3    56.7/37.9/49.9    63.5/38.6/49.9    63.4/48.1/50.0    29.3/33.7/45.7    36.1/34.4/43.8
-//   fp32  84 MB    17.9/24.0/34.2    17.8/24.0/34.3    22.3/23.9/34.2    38.7/25.2/34.2    18.4/20.7/31.0    18.2/20.1/30.2
-//        104 MB    21.7/29.2/41.0    25.4/29.1/41.3    42.2/29.0/41.0    47.3/32.7/40.9    22.1/25.2/37.8    24.3/25.3/36.2
-//        134 MB    25.8/34.9/50.3    44.3/34.8/50.2    58.7/35.1/50.3    59.3/43.6/50.2    26.1/29.9/46.5    32.5/30.6/44.2
+//               1 buffer        3 in turn       4               8               fresh, 1        fresh, 4
+// bf16   67 MB  16.7/20.9/27.8  16.6/20.7/27.9  18.4/20.7/27.7  33.5/21.3/27.8  17.0/19.0/26.2  19.3/19.0/25.4
+//        92 MB  21.2/26.9/35.3  24.1/26.9/35.0  36.7/27.0/35.1  44.1/28.2/34.8  21.3/23.5/32.2  22.7/23.4/31.4
+//       100 MB  22.8/29.6/38.3  28.0/29.4/38.2  45.8/29.6/38.3  47.8/31.4/38.1  23.2/26.2/35.1  25.6/25.7/33.7
+//       134 MB  29.1/38.3/50.3  56.7/37.9/49.9  63.5/38.6/49.9  63.4/48.1/50.0  29.3/33.7/45.7  36.1/34.4/43.8
+// fp32   84 MB  17.9/24.0/34.2  17.8/24.0/34.3  22.3/23.9/34.2  38.7/25.2/34.2  18.4/20.7/31.0  18.2/20.1/30.2
+//       104 MB  21.7/29.2/41.0  25.4/29.1/41.3  42.2/29.0/41.0  47.3/32.7/40.9  22.1/25.2/37.8  24.3/25.3/36.2
+//       134 MB  25.8/34.9/50.3  44.3/34.8/50.2  58.7/35.1/50.3  59.3/43.6/50.2  26.1/29.9/46.5  32.5/30.6/44.2
 // Right after what writes logits in a model, the step takes, stores / select /
 // the kernel before (events around it, 3 us of them): after the output
 // projection (K = 4,096, whose weights pass the cache) 33 MB bf16 18.3 / 19.6 /
@@ -1967,9 +1967,10 @@ int compute_units() {
 // more than one): one where that gives at most 4 workgroups per compute unit
 // or a row has no more tiles than a workgroup wavefronts (a second one would be
 // empty and cost registers: 4,000 x 2,049 bf16 23.8 us with one, 32.1 with two,
-// 28.9 with a key per element; 4,000 x 8,192 25.8, 32.4 and 28.8); otherwise as many as it takes for all workgroups to be on the GPU at once, 5
-// per compute unit (the pair's registers), since each begins with its
-// sequence's walk and ends with two atomics.  us, 1 / 2 / 4 / 8 tiles a
+// 28.9 with a key per element; 4,000 x 8,192 25.8, 32.4 and 28.8); otherwise as
+// many as it takes for all workgroups to be on the GPU at once, 5 per compute
+// unit (the pair's registers), since each begins with its sequence's walk and
+// ends with two atomics.  us, 1 / 2 / 4 / 8 tiles a
 // wavefront: 8 x 32,000 bf16 (32 workgroups of one tile) 7.1 / 8.0 / 10.4 / 15.3;
 // 64 x 151,936 (1,216) 11.5 / 11.1 / 13.6 / 18.7; 128 x 151,936 (2,432) 11.6 /
 // 10.2 / 13.5 / 18.9; 200 x 151,665 (3,800) 23.1 / 21.1 / 18.4 / 24.0;
@@ -2134,10 +2135,9 @@ void launch_apply(void *logits, bool bf16, const uint32_t *bitmask, int32_t B, i
 }
 
 // Whether the single-launch decoding step masks an element per thread: short
-// rows, as the step does, and grids of few workgroups, where a wavefront's pass
-// over a tile, whose code the advance before it has pushed out of the
-// instruction cache, is the longer way; in fp32, half the elements a tile, only
-// up to 4,096 logits a row.  us with real tokens, elements / tiles: 64 x 2,049
+// rows, as the step does, and grids of few workgroups, where nothing hides a
+// wavefront's pass over a tile, the longer way; in fp32, half the elements a
+// tile, only up to 4,096 logits a row.  us with real tokens, elements / tiles: 64 x 2,049
 // bf16 6.2 / 7.7, 8 x 65,537 7.7 / 8.5, 64 x 65,537 (1,088 workgroups) 9.3 / 9.9,
 // 512 x 8,193 (1,536) 9.0 / 9.3, 128 x 65,536 (2,048) 13.7 / 10.4; fp32 64 x 3,073
 // 6.6 / 7.0, 64 x 4,097 6.95 / 7.0, 64 x 8,192 7.3 / 7.2.
